@@ -120,8 +120,6 @@ __global__ __launch_bounds__(NCW * 64 + 256) void k_scan_bwd(Params p) {
   typedef typename Mma<E>::frag FR;
   typedef ScanBwdRing<E, DK, BV> R;
   constexpr int NA = R::NA;
-  // fp32 operands take 4-deep k-steps; their long k loops are only partly unrolled
-  constexpr int UKD = NKS > 4 ? 4 : NKS;
   __shared__ ScanBwdSmem<E, DK, BV> sm;
   const int tid = threadIdx.x, lane = tid & 63, w = wave_id(tid);
   const int prod = w - NCW;                  // 0-3 for the producer waves, negative otherwise
@@ -242,7 +240,7 @@ __global__ __launch_bounds__(NCW * 64 + 256) void k_scan_bwd(Params p) {
       f4 dt[NBW];
 #pragma unroll
       for (int j = 0; j < NBW; ++j) dt[j] = zero4();
-#pragma unroll UKD
+#pragma unroll
       for (int ks = 0; ks < NKS; ++ks) {
         const FR kB = tile_frag<E, R::RK>(rx + R::XK, 16 * cb, ks * KS, lane);
 #pragma unroll
@@ -630,12 +628,8 @@ __global__ __launch_bounds__(INTRA_THREADS) __attribute__((amdgpu_waves_per_eu(i
 #pragma unroll
       for (int ks = 0; ks < NKK; ++ks) {
         const int kbyte = (ks * KS + (lane >> 4) * Mma<E>::KPL) * (int)ES;
-        if constexpr (sizeof(E) == 2) {
-          const uint4 z = make_uint4(0, 0, 0, 0);
-          *(uint4*)(sm.ring[0] + SM::OK + tile_off<RK>(rr, kbyte)) = kz != 0.f ? __builtin_bit_cast(uint4, kf[ks]) : z;
-        } else {
-          *(float*)(sm.ring[0] + SM::OK + tile_off<RK>(rr, kbyte)) = kz * kf[ks];
-        }
+        const uint4 z = make_uint4(0, 0, 0, 0);
+        *(uint4*)(sm.ring[0] + SM::OK + tile_off<RK>(rr, kbyte)) = kz != 0.f ? __builtin_bit_cast(uint4, kf[ks]) : z;
       }
     }
     char* t = sm.ring[vt & 1];

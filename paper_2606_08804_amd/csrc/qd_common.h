@@ -1,7 +1,8 @@
 // Shared device-side building blocks of the Q-Delta HIP kernels (gfx950).
 //
 //  * MFMA traits: bf16 operands use v_mfma_f32_16x16x32_bf16, fp32 operands
-//    v_mfma_f32_16x16x4_f32; both accumulate in fp32.  Lane layouts (wave64):
+//    four v_mfma_f32_16x16x4_f32 per step; both accumulate in fp32.  Lane
+//    layouts (wave64):
 //      A (16 x K)  lane l holds row l%16, k = KPL*(l/16) .. +KPL-1
 //      B (K x 16)  lane l holds col l%16, k = KPL*(l/16) .. +KPL-1
 //      C (16 x 16) lane l holds col l%16, rows 4*(l/16) .. +3
@@ -23,7 +24,7 @@ typedef float f4 __attribute__((ext_vector_type(4)));
 
 // Lower-triangular chunk operands (T, M, P) are stored with exact zeros above
 // the 16 x 16 block diagonal, so products with them may skip those k blocks
-// or not: the fp32 forms (16 k steps per chunk) skip them; the bf16 forms
+// or not: the fp32 forms (four k steps per chunk) skip them; the bf16 forms
 // (two k steps) run every block, which keeps the waves' work equal and each
 // phase one basic block whose LDS reads can all be issued ahead of the MFMAs.
 template <typename E>
@@ -47,12 +48,18 @@ template <> struct Mma<__bf16> {
   }
 };
 
+// fp32: one step is 16 k values, four per lane, so that a fragment is one
+// 16-byte LDS read (as for bf16) instead of four 4-byte ones.  Instruction j
+// of the step takes element j of every lane's fragment, the k values j, 4 + j,
+// 8 + j and 12 + j; the two operands agree on that order.
 template <> struct Mma<float> {
-  static constexpr int KS = 4;
-  static constexpr int KPL = 1;
-  typedef float frag;
+  static constexpr int KS = 16;
+  static constexpr int KPL = 4;
+  typedef f4 frag;
   __device__ static inline f4 mma(frag a, frag b, f4 c) {
-    return __builtin_amdgcn_mfma_f32_16x16x4f32(a, b, c, 0, 0, 0);
+#pragma unroll
+    for (int j = 0; j < 4; ++j) c = __builtin_amdgcn_mfma_f32_16x16x4f32(a[j], b[j], c, 0, 0, 0);
+    return c;
   }
 };
 
@@ -101,13 +108,15 @@ template <> struct Frag<__bf16> {
 };
 
 template <> struct Frag<float> {
-  template <typename S>
-  __device__ static inline float load(KMaj<S> v, int i0, int k0, int lane) {
-    return tof(v.p[(size_t)(i0 + (lane & 15)) * v.ld + k0 + (lane >> 4)]);
+  __device__ static inline f4 load(KMaj<float> v, int i0, int k0, int lane) {
+    return *(const f4*)(v.p + (size_t)(i0 + (lane & 15)) * v.ld + k0 + (lane >> 4) * 4);
   }
-  template <typename S>
-  __device__ static inline float load(IMaj<S> v, int i0, int k0, int lane) {
-    return tof(v.p[(size_t)(k0 + (lane >> 4)) * v.ld + i0 + (lane & 15)]);
+  __device__ static inline f4 load(IMaj<float> v, int i0, int k0, int lane) {
+    const float* s = v.p + (size_t)(k0 + (lane >> 4) * 4) * v.ld + i0 + (lane & 15);
+    f4 r;
+#pragma unroll
+    for (int j = 0; j < 4; ++j) r[j] = s[(size_t)j * v.ld];
+    return r;
   }
 };
 
@@ -349,7 +358,10 @@ __device__ inline typename Mma<E>::frag tile_tr_frag(const char* t, int k0, int 
     const v4b hi = __builtin_amdgcn_ds_read_tr16_b64_v4bf16((lp)(uintptr_t)(uint32_t)(uintptr_t)(b + (tr_y<RB>(lane, 4) ^ (2 * j0))));
     return __builtin_shufflevector(lo, hi, 0, 1, 2, 3, 4, 5, 6, 7);
   } else {
-    return *(const float*)(t + tile_off<RB>(k0 + (lane >> 4), 4 * (j0 + (lane & 15))));
+    f4 r;
+#pragma unroll
+    for (int j = 0; j < 4; ++j) r[j] = *(const float*)(t + tile_off<RB>(k0 + (lane >> 4) * 4 + j, 4 * (j0 + (lane & 15))));
+    return r;
   }
 }
 // MFMA fragment of the TRANSPOSE of a row-major 16-bit LDS matrix: with
@@ -372,8 +384,11 @@ __device__ inline bf8 tr_frag<__bf16>(const __bf16* base, int ld, int k0, int j0
   return __builtin_shufflevector(lo, hi, 0, 1, 2, 3, 4, 5, 6, 7);
 }
 template <>
-__device__ inline float tr_frag<float>(const float* base, int ld, int k0, int j0, int lane) {
-  return base[(size_t)(k0 + (lane >> 4)) * ld + j0 + (lane & 15)];
+__device__ inline f4 tr_frag<float>(const float* base, int ld, int k0, int j0, int lane) {
+  f4 r;
+#pragma unroll
+  for (int j = 0; j < 4; ++j) r[j] = base[(size_t)(k0 + (lane >> 4) * 4 + j) * ld + j0 + (lane & 15)];
+  return r;
 }
 
 
