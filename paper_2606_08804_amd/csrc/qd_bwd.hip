@@ -77,7 +77,7 @@ struct alignas(16) ScanBwdSmem {
 };
 
 // One workgroup per (sequence, head, Dv tile of BV value rows): NCW compute
-// waves (eight for bf16, two per SIMD, as in the forward scan) and four
+// waves (eight, four with 16-row tiles, as in the forward scan) and four
 // producer waves; reverse pass over the chunks.  The exit-state gradient tile
 // dS'^T (Dk x BV) lives in fp32 MFMA accumulators, split over the compute
 // waves by key blocks (and value blocks when there are more waves than key
@@ -980,14 +980,15 @@ static hipError_t launch_bwd_t(const Params& p, hipStream_t st) {
   const int nb = ((units + 7) / 8) * 8 * (DV / bv);
   if (nb > 0) {
     prof_mark(ST_SCAN_BWD, 0, st);
-    constexpr int NCW = sizeof(E) == 2 ? 8 : 4;   // compute waves: two per SIMD for bf16
-    if constexpr (scan_bv_max<E, DV>() == 64) {
-      if (bv == 64)
-        hipLaunchKernelGGL((k_scan_bwd<E, DK, DV, 64, NCW>), dim3(nb), dim3(NCW * 64 + 256), 0, st, p);
-      else
-        hipLaunchKernelGGL((k_scan_bwd<E, DK, DV, 32, NCW>), dim3(nb), dim3(NCW * 64 + 256), 0, st, p);
+    const dim3 b8(8 * 64 + 256);   // compute and producer waves as in the forward scan
+    if (bv == 64) {
+      if constexpr (scan_bv_max<E, DV>() == 64)
+        hipLaunchKernelGGL((k_scan_bwd<E, DK, DV, 64, 8>), dim3(nb), b8, 0, st, p);
+    } else if (bv == 16) {
+      if constexpr (scan_bv_min<E>() == 16)
+        hipLaunchKernelGGL((k_scan_bwd<E, DK, DV, 16, 4>), dim3(nb), dim3(4 * 64 + 256), 0, st, p);
     } else {
-      hipLaunchKernelGGL((k_scan_bwd<E, DK, DV, 32, NCW>), dim3(nb), dim3(NCW * 64 + 256), 0, st, p);
+      hipLaunchKernelGGL((k_scan_bwd<E, DK, DV, 32, 8>), dim3(nb), b8, 0, st, p);
     }
     prof_mark(ST_SCAN_BWD, 1, st);
   }

@@ -548,9 +548,16 @@ template <typename E, int DV>
 constexpr int scan_bv_max() {
   return (sizeof(E) == 2 && DV >= 64) ? 64 : 32;
 }
+// fp32 tiles go down to 16 rows while every one still has a CU to itself: a
+// chunk's serial chain there is bound by the fp32 matrix instructions, whose
+// number per workgroup follows the tile's rows (12 pairs of 1003 tokens, d_v
+// 128: forward scan 75 -> 54 us, backward scan 69 -> 51 us).
+template <typename E>
+constexpr int scan_bv_min() { return sizeof(E) == 4 ? 16 : 32; }
 template <typename E, int DV>
 inline int scan_bv(int units) {
   if (scan_bv_max<E, DV>() == 64 && (long long)units * (DV / 64) >= 2LL * device_cu_count()) return 64;
+  if (scan_bv_min<E>() == 16 && (long long)units * (DV / 16) <= device_cu_count()) return 16;
   return 32;
 }
 

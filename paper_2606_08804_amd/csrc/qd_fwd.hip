@@ -424,10 +424,14 @@ struct alignas(16) ScanFwdSmem {
 
 // One workgroup per (sequence, head, Dv tile of BV value rows): NCW compute
 // waves and four producer waves (one wave alone issues direct loads at only
-// about 12 bytes per clock).  bf16 runs eight compute waves, two per SIMD:
+// about 12 bytes per clock).  Eight compute waves, two per SIMD (four with
+// 16-row tiles, which have one value block):
 // a single wave reads LDS at only about 26 bytes per clock (16 with transpose
 // reads), so a chunk's fragment reads take half as long on each of twice as
-// many waves.  The state tile S^T (Dk x BV) lives in fp32 MFMA accumulators
+// many waves (fp32, 12 (sequence, head) pairs of 1003 tokens, d_k 64, d_v 128:
+// 115 us with four waves and 4-byte operand reads, 75 us with eight and
+// 16-byte reads, 54 us in 16-row tiles; the fp32 matrix instructions of one
+// chunk alone take 6.1k cycles per SIMD in a 32-row tile).  The state tile S^T (Dk x BV) lives in fp32 MFMA accumulators
 // across the whole sequence, split over the compute waves by key blocks (and
 // value blocks when there are more waves than key blocks); compute wave w
 // owns chunk rows 16 (w & 3).. of every C-row result and a range of its
@@ -783,9 +787,9 @@ __global__ __launch_bounds__(NCW * 64 + 256) void k_scan_fwd(Params p) {
       if (saved) {
         // D rows of this tile into the saved context (rows past the chunk are
         // zero), whose 32-column tiles are contiguous C x 32 blocks: each
-        // workgroup writes whole blocks
-        constexpr int VEC = 16 / sizeof(E), PR = BV / VEC, PT = 32 / VEC;
-        E* dbase = (E*)p.savedD + gi * C * DV + (size_t)v0 * C;
+        // workgroup writes whole blocks (a 16-row tile: half of each row)
+        constexpr int VEC = 16 / sizeof(E), PR = BV / VEC, PT = (BV < 32 ? BV : 32) / VEC;
+        E* dbase = (E*)p.savedD + gi * C * DV + (size_t)(v0 & ~31) * C + (v0 & 31);
         for (int idx = tid; idx < C * PR; idx += NCT) {
           const int sub = idx / (C * PT), r = (idx / PT) % C, cc = (idx % PT) * VEC;
           *(uint4*)(dbase + (size_t)sub * C * 32 + (size_t)r * 32 + cc) = *(const uint4*)&sm.D[r][sub * 32 + cc];
@@ -856,16 +860,17 @@ static hipError_t launch_fwd_t(const Params& p, int in_bwd, int with_scan, hipSt
     const int nb = ((units + 7) / 8) * 8 * (DV / bv);
     if (nb > 0) {
       prof_mark(ST_SCAN_FWD, 0, st);
-      // bf16: eight compute waves (two per SIMD, each with half of the LDS
-      // reads of a chunk); fp32: four
-      constexpr int NCW = sizeof(E) == 2 ? 8 : 4;
-      if constexpr (scan_bv_max<E, DV>() == 64) {
-        if (bv == 64)
-          hipLaunchKernelGGL((k_scan_fwd<E, DK, DV, 64, NCW, SEG_NONE>), dim3(nb), dim3(NCW * 64 + 256), 0, st, p);
-        else
-          hipLaunchKernelGGL((k_scan_fwd<E, DK, DV, 32, NCW, SEG_NONE>), dim3(nb), dim3(NCW * 64 + 256), 0, st, p);
+      // eight compute waves: two per SIMD, each with half of the LDS reads of a
+      // chunk; 16-row tiles have one value block, so four
+      const dim3 b8(8 * 64 + 256);
+      if (bv == 64) {
+        if constexpr (scan_bv_max<E, DV>() == 64)
+          hipLaunchKernelGGL((k_scan_fwd<E, DK, DV, 64, 8, SEG_NONE>), dim3(nb), b8, 0, st, p);
+      } else if (bv == 16) {
+        if constexpr (scan_bv_min<E>() == 16)
+          hipLaunchKernelGGL((k_scan_fwd<E, DK, DV, 16, 4, SEG_NONE>), dim3(nb), dim3(4 * 64 + 256), 0, st, p);
       } else {
-        hipLaunchKernelGGL((k_scan_fwd<E, DK, DV, 32, NCW, SEG_NONE>), dim3(nb), dim3(NCW * 64 + 256), 0, st, p);
+        hipLaunchKernelGGL((k_scan_fwd<E, DK, DV, 32, 8, SEG_NONE>), dim3(nb), b8, 0, st, p);
       }
       prof_mark(ST_SCAN_FWD, 1, st);
     }
@@ -952,7 +957,7 @@ static hipError_t launch_fwd_seg_t(const Params& p, hipStream_t st) {
   if (e != hipSuccess) return e;
   const int units = p.N * p.H;
   if (units == 0) return hipSuccess;
-  constexpr int NCW = sizeof(E) == 2 ? 8 : 4;
+  constexpr int NCW = 8;
   constexpr int BW = scan_bv_max<E, DV>();     // 64 for bf16, else 32
   const int su8 = ((units * p.n_seg + 7) / 8) * 8;
   const bool out_wide = BW == 64 && (long long)units * p.n_seg * (DV / 64) >= device_cu_count();
