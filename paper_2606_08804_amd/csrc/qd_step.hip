@@ -95,86 +95,263 @@ __global__ __launch_bounds__(NTHREADS) void k_step(int DV, int nrb, const E* __r
   }
 }
 
-hipError_t launch_step(int N, int H, int Dk, int Dv, int dtype, const void* q, const void* k,
-                       const void* v, const float* beta, const float* lam, float lam_c, const float* la,
-                       float* state, void* o, hipStream_t st) {
+// The same for a few tokens per sequence, the state staying in registers
+// between them, from S0 (NULL: zero) to S (NULL: not wanted): sequence n spans
+// tokens [cu[n], cu[n+1]) when cu is given (clamped to [0, T_total]), else
+// [n T, (n + 1) T); token t of head h sits at row t H + h.
+template <typename E, int DK>
+__global__ __launch_bounds__(NTHREADS) void k_steps(int T, const int* __restrict__ cu, int T_total, int H,
+                                                  int DV, int nrb, const E* __restrict__ q,
+                                                  const E* __restrict__ k, const E* __restrict__ v,
+                                                  const float* __restrict__ beta,
+                                                  const float* __restrict__ lam, float lam_c,
+                                                  const float* __restrict__ la, const float* __restrict__ S0,
+                                                  float* __restrict__ S, E* __restrict__ o) {
+  constexpr int LPR = DK / 4;            // lanes per state row
+  constexpr int RPB = NTHREADS / LPR;    // rows per workgroup pass
+  constexpr int RPT = STEP_RPT;          // passes (rows per lane group)
+  const size_t u = blockIdx.x / nrb;     // (sequence, head) unit
+  const int rb = blockIdx.x % nrb;       // block of RPB * RPT state rows
+  const int tid = threadIdx.x;
+  const int row0 = rb * RPB * RPT + tid / LPR;
+  const int c0 = (tid % LPR) * 4;
+  const int n = (int)(u / H);
+  const int t0 = cu ? min(max(cu[n], 0), T_total) : n * T;
+  const int t1 = cu ? min(max(cu[n + 1], t0), T_total) : t0 + T;
+  size_t a = (size_t)t0 * H + u % H;     // row of the token
+  float qv[4], kv[4], bt, lm, la_, vr[RPT];
+  auto load = [&]() {
+#pragma unroll
+    for (int j = 0; j < 4; ++j) {
+      qv[j] = tof(q[a * DK + c0 + j]);
+      kv[j] = tof(k[a * DK + c0 + j]);
+    }
+    lm = lam ? lam[a] : lam_c;
+    bt = beta[a];
+    la_ = la ? la[a] : 0.f;
+  };
+  auto load_v = [&]() {
+#pragma unroll
+    for (int i = 0; i < RPT; ++i) {
+      const int row = row0 + i * RPB;
+      vr[i] = row < DV ? tof(v[a * DV + row]) : 0.f;
+    }
+  };
+  f4 s[RPT];
+#pragma unroll
+  for (int i = 0; i < RPT; ++i) {        // rows past DV: the whole lane group skips them
+    const int row = row0 + i * RPB;
+    s[i] = S0 && row < DV ? *(const f4*)(S0 + (u * DV + row) * DK + c0) : zero4();
+  }
+  if (t0 < t1) {
+    load();
+    load_v();
+  }
+  for (int t = t0; t < t1; ++t) {
+    const size_t at = a;
+    float qt[4], kt[4], xv[4], vt[RPT];
+    const float be = bt, lmt = lm, al = la ? __expf(la_) : 1.f;
+#pragma unroll
+    for (int j = 0; j < 4; ++j) {
+      qt[j] = qv[j];
+      kt[j] = kv[j];
+      xv[j] = kt[j] + lmt * qt[j];
+    }
+#pragma unroll
+    for (int i = 0; i < RPT; ++i) vt[i] = vr[i];
+    if (t + 1 < t1) {                    // the next token's operands, in flight during this one
+      a += H;
+      load();
+      load_v();
+    }
+    float px[RPT];
+#pragma unroll
+    for (int i = 0; i < RPT; ++i) {
+      px[i] = 0.f;
+#pragma unroll
+      for (int j = 0; j < 4; ++j) px[i] += s[i][j] * xv[j];
+    }
+#pragma unroll
+    for (int i = 0; i < RPT; ++i) px[i] = row_sum<LPR>(px[i]);
+    float oq[RPT];
+#pragma unroll
+    for (int i = 0; i < RPT; ++i) {
+      const float e = be * (vt[i] - al * px[i]);
+      oq[i] = 0.f;
+#pragma unroll
+      for (int j = 0; j < 4; ++j) {
+        s[i][j] = al * s[i][j] + e * kt[j];
+        oq[i] += s[i][j] * qt[j];
+      }
+      const int row = row0 + i * RPB;
+      if (row < DV && S && t + 1 == t1) *(f4*)(S + (u * DV + row) * DK + c0) = s[i];
+    }
+#pragma unroll
+    for (int i = 0; i < RPT; ++i) oq[i] = row_sum<LPR>(oq[i]);
+    if ((tid % LPR) == 0) {
+#pragma unroll
+      for (int i = 0; i < RPT; ++i) {
+        const int row = row0 + i * RPB;
+        if (row < DV) o[at * DV + row] = fromf<E>(oq[i]);
+      }
+    }
+  }
+  if (t0 == t1 && S) {                   // no token: the state passes through
+#pragma unroll
+    for (int i = 0; i < RPT; ++i) {
+      const int row = row0 + i * RPB;
+      if (row < DV) *(f4*)(S + (u * DV + row) * DK + c0) = s[i];
+    }
+  }
+}
+
+// T < 0: the decode step, S updated in place; else T tokens (or cu) from S0 to S.
+static hipError_t step_at(int N, int T, const int* cu, int T_total, int H, int Dk, int Dv, int dtype, const void* q,
+                          const void* k, const void* v, const float* beta, const float* lam, float lam_c,
+                          const float* la, const float* S0, float* S, void* o, hipStream_t st) {
   if (N == 0) return hipSuccess;
+  if (!((dtype == 1 || dtype == 0) && (Dk == 128 || Dk == 64))) return hipErrorInvalidValue;
   const int RPB = NTHREADS / (Dk / 4) * STEP_RPT;   // state rows per workgroup
   const int nrb = (Dv + RPB - 1) / RPB;
+  const int stage = T < 0 ? ST_STEP : ST_REC_FWD;
   dim3 grid((unsigned)((size_t)N * H * nrb));
-#define QD_STEP(ET, DKV)                                                                        \
-  hipLaunchKernelGGL((k_step<ET, DKV>), grid, dim3(NTHREADS), 0, st, Dv, nrb, (const ET*)q,     \
-                     (const ET*)k, (const ET*)v, beta, lam, lam_c, la, state, (ET*)o)
-  if (!((dtype == 1 || dtype == 0) && (Dk == 128 || Dk == 64))) return hipErrorInvalidValue;
-  prof_mark(ST_STEP, 0, st);
+#define QD_STEP(ET, DKV)                                                                               \
+  do {                                                                                                 \
+    if (T < 0)                                                                                         \
+      hipLaunchKernelGGL((k_step<ET, DKV>), grid, dim3(NTHREADS), 0, st, Dv, nrb, (const ET*)q,        \
+                         (const ET*)k, (const ET*)v, beta, lam, lam_c, la, S, (ET*)o);                 \
+    else                                                                                               \
+      hipLaunchKernelGGL((k_steps<ET, DKV>), grid, dim3(NTHREADS), 0, st, T, cu, T_total, H, Dv, nrb,  \
+                         (const ET*)q, (const ET*)k, (const ET*)v, beta, lam, lam_c, la, S0, S, (ET*)o); \
+  } while (0)
+  prof_mark(stage, 0, st);
   if (dtype == 1 && Dk == 128) QD_STEP(__bf16, 128);
   else if (dtype == 1 && Dk == 64) QD_STEP(__bf16, 64);
   else if (dtype == 0 && Dk == 128) QD_STEP(float, 128);
   else QD_STEP(float, 64);
-  prof_mark(ST_STEP, 1, st);
+  prof_mark(stage, 1, st);
 #undef QD_STEP
   return hipGetLastError();
 }
 
-// Fully recurrent forward over whole sequences (Sec. 3.3, Eq. (qdelta_decay)
-// token by token; the paper offers this form beside the chunkwise one).
-//
-// A state row is owned by a group of LPR = 8 lanes, each holding Dk/8
-// columns, so both per-token row dot products reduce in three DPP steps;
-// the NT/8 lane groups of a workgroup hold RPT rows each in registers for
-// the whole sequence: the state is read once (initial state or zero) and
-// written once (final state).  Both row dot products use the state before
-// the update (o_t = alpha S_{t-1} q + e (k . q)), so they reduce side by
-// side, and the decay multiplies a scale instead of every element (the rows
-// are held as true state / scale, folded back once per block), so the
-// update is one FMA per element.  Tokens are processed in blocks of
-// TB: the block's q, k, v slice and gates are staged in LDS (two buffers;
-// block b + 1 is loaded into registers while block b is computed, then
-// written to the other buffer), so each token reads LDS, not HBM.
-// Sequence n of unit u = n * H + h spans tokens [cu[n], cu[n+1]) when cu is
-// given (clamped to [0, T_total]), else [n * T, (n + 1) * T); token t of head
-// h sits at row t * H + h of the activations and gates.
-typedef unsigned int u32x4 __attribute__((ext_vector_type(4)));
-
-// Sum over each aligned group of 8 lanes, result in every lane of the group,
-// with DPP lane moves (no LDS round trip): lanes xor 1 and xor 2 (quad permutations [1,0,3,2] and [2,3,0,1]) give each
-// quad its total; the half-row mirror (lane i <-> 7 - i within 8) then adds
-// the other quad's total.
-__device__ inline float group8_sum(float x) {
-  x += dpp_mov<0xB1>(x);
-  x += dpp_mov<0x4E>(x);
-  x += dpp_mov<0x141>(x);
-  return x;
+hipError_t launch_step(int N, int H, int Dk, int Dv, int dtype, const void* q, const void* k,
+                       const void* v, const float* beta, const float* lam, float lam_c, const float* la,
+                       float* state, void* o, hipStream_t st) {
+  return step_at(N, -1, nullptr, 0, H, Dk, Dv, dtype, q, k, v, beta, lam, lam_c, la, nullptr, state, o, st);
 }
 
-template <typename E, int DK, int RPT, int NT>
-__global__ __launch_bounds__(NT) void k_rec_fwd(
-    int T, int H, int DV, int nrb, const int* __restrict__ cu, int T_total, const E* __restrict__ q,
+// Fully recurrent forward over whole sequences (Sec. 3.3, Eq. (qdelta_decay)
+// token by token; the paper offers this form beside the chunkwise one), in
+// fp32 throughout.
+//
+// One wave owns 16 VB value rows of one (sequence, head) and walks its tokens
+// in blocks of RTB = 16.  Within a block, with entry state S, decay products
+// g_t = alpha_1..alpha_t, Gam_ti = alpha_{i+1}..alpha_t and x = k + lambda q,
+// unrolling the recurrence gives
+//
+//   e_t = beta_t (v_t - g_t S x_t) - sum_{i<t} beta_t Gam_ti (k_i . x_t) e_i
+//   o_t = g_t S q_t + sum_{i<=t} Gam_ti (k_i . q_t) e_i
+//   S  <- g_C S + sum_i Gam_Ci e_i k_i^T
+//
+// so the products with the state, S k_t and S q_t for 16 tokens and the rank-16
+// update, are fp32 matrix products (16x16x4), and only the triangular part is
+// left to the vector ALU: a lane holds one value row there and substitutes
+// token by token with coefficients broadcast from LDS (so a row never sees a
+// later token).  The state lives in registers as S^T tiles in the matrix
+// result layout, which is the layout of the operand the next block's S k_t
+// takes, so it passes through no LDS.  Decays are multiplied up, never divided
+// or exponentiated from sums, so alpha = 0 is exact.
+//
+// 64 sequences x 16 heads, d 128, bf16: 16 tokens move 151 MB and take 2.6e9
+// matrix operations; vector-ALU row sums over the whole state, as in the step
+// kernel, took 75 us at T = 16 and 190 us at T = 64.
+typedef unsigned int u32x4 __attribute__((ext_vector_type(4)));
+constexpr int RTB = 16;
+#define REC_FENCE __builtin_amdgcn_sched_barrier(0)
+
+// State tile kt = 2 p + h holds the key columns 32 p + 8 (m >> 2) + 4 h + (m & 3)
+// for m = 0..15: a lane's rows of the tile pair are eight consecutive columns,
+// one 16-byte bf16 read of K or Q and 32 contiguous bytes of the state.
+__device__ inline int rec_col(int kt, int m) { return 32 * (kt >> 1) + 8 * (m >> 2) + 4 * (kt & 1) + (m & 3); }
+
+template <typename E, int DK, int VB>
+struct alignas(16) RecFwdSmem {
+  static constexpr int NV = 16 * VB, P = Pad<E>::v;
+  static constexpr int XB = RTB * (NV + 4) * 4, QB = RTB * (DK + P) * (int)sizeof(E);
+  alignas(16) E k[RTB][DK + P];
+  alignas(16) char qx[QB > XB ? QB : XB];      // Q, then g_t S q_t per value row
+  alignas(16) float x[RTB][NV + 4];            // right-hand sides, then Gam_Ct e_t
+  alignas(16) E v[RTB][NV];
+  alignas(16) float A[RTB][RTB], Pm[RTB][RTB]; // coefficients of the triangular part
+  alignas(16) float gate[4][RTB];              // beta, lambda, alpha
+};
+
+// Four K (or Q) values of one row as fp32 operands of the tile pair p.
+template <typename E>
+__device__ inline void rec_row8(const E* src, f4& lo, f4& hi) {
+  if constexpr (sizeof(E) == 2) {
+    const bf8 r = *(const bf8*)src;
+#pragma unroll
+    for (int j = 0; j < 4; ++j) {
+      lo[j] = (float)r[j];
+      hi[j] = (float)r[4 + j];
+    }
+  } else {
+    lo = *(const f4*)src;
+    hi = *(const f4*)(src + 4);
+  }
+}
+
+// K^T operand of tile kt: tokens 4 (lane >> 4) .. +3 of column rec_col(kt, lane & 15).
+template <typename E>
+__device__ inline f4 rec_tok4(const E* k, int ld, int kt, int lane) {
+  const int g = lane >> 4, L = lane & 15;
+  f4 r;
+  if constexpr (sizeof(E) == 2) {
+    typedef __bf16 v4b __attribute__((ext_vector_type(4)));
+    typedef __attribute__((address_space(3))) v4b* lp;
+    // LDS transpose read: lane L names the four columns from rec_col(kt, 4 (L & 3))
+    // of row L >> 2 and receives column L of the group's 4 x 16 block
+    const E* a = k + (size_t)(4 * g + (L >> 2)) * ld + rec_col(kt, 4 * (L & 3));
+    const v4b t = __builtin_amdgcn_ds_read_tr16_b64_v4bf16((lp)(uintptr_t)(uint32_t)(uintptr_t)a);
+#pragma unroll
+    for (int j = 0; j < 4; ++j) r[j] = (float)t[j];
+  } else {
+#pragma unroll
+    for (int j = 0; j < 4; ++j) r[j] = k[(size_t)(4 * g + j) * ld + rec_col(kt, L)];
+  }
+  return r;
+}
+
+// Value blocks per wave where the launch fills the chip: wide tiles share the
+// K, Q reads and the Gram products over more rows, as many as the register
+// file takes at two waves per SIMD or more.
+template <typename E, int DK>
+constexpr int rec_wide() { return sizeof(E) == 2 && DK == 128 ? 4 : 2; }
+// Waves per SIMD that the register need allows (the state takes 4 VB DK / 16
+// registers of a lane, the next block's pieces and the products the rest).
+template <typename E, int DK, int VB>
+constexpr int rec_waves() { return sizeof(E) == 4 ? (DK == 64 ? 2 : VB == 1 ? 2 : 2) : VB == 4 ? 2 : VB == 2 ? 3 : DK == 128 ? 2 : 4; }
+
+template <typename E, int DK, int VB>
+__global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(rec_waves<E, DK, VB>(), rec_waves<E, DK, VB>()))) void k_rec_fwd(
+    int T, int H, int DV, int units, int ntile, const int* __restrict__ cu, int T_total, const E* __restrict__ q,
     const E* __restrict__ k, const E* __restrict__ v, const float* __restrict__ beta,
     const float* __restrict__ lam, float lam_c, const float* __restrict__ la, const float* __restrict__ S0,
     float* __restrict__ Sfin, E* __restrict__ o) {
-  constexpr int LPR = 8;                       // lanes per state row (group8_sum)
-  constexpr int CPL = DK / LPR;                // columns per lane
-  constexpr int NG = NT / LPR;                 // lane groups (rows per pass)
-  constexpr int R = NG * RPT;                  // state rows per workgroup
-  constexpr int TB = 16;                       // tokens per staged block
+  constexpr int NV = 16 * VB, NKT = DK / 16;
   constexpr int EPP = 16 / (int)sizeof(E);     // elements per 16-byte piece
-  constexpr int QKP = TB * DK / EPP;           // pieces of one block of q (or k)
-  constexpr int VP = TB * R / EPP;             // pieces of one block of v
-  constexpr int QKT = (QKP + NT - 1) / NT;
-  constexpr int VT = (VP + NT - 1) / NT;
-  static_assert(CPL % 4 == 0, "columns per lane");
-  __shared__ __align__(16) E qs[2][TB * DK];
-  __shared__ __align__(16) E ks[2][TB * DK];
-  __shared__ __align__(16) E vs[2][TB * R];
-  __shared__ float gs[2][3 * TB];
-
-  const int u = blockIdx.x / nrb;              // (sequence, head) unit
-  const int rb = blockIdx.x % nrb;
-  const int n = u / H, h = u % H;
-  const int tid = threadIdx.x;
-  const int grp = tid / LPR;
-  const int c0 = (tid % LPR) * CPL;
+  constexpr int QKN = RTB * DK / EPP / 64;     // pieces of one block of q (or k) per lane
+  constexpr int VP = RTB * NV / EPP, VN = (VP + 63) / 64;
+  typedef RecFwdSmem<E, DK, VB> SM;
+  constexpr int LDK = DK + SM::P, LDX = NV + 4;
+  __shared__ SM sm;
+  E* const qs = (E*)sm.qx;
+  float* const xq = (float*)sm.qx;
+  int u, vt;                                   // all value tiles of a unit on one XCD: they share k and q
+  if (!xcd_unit_tile(blockIdx.x, units, ntile, u, vt)) return;
+  const int n = u / H, h = u % H, v0 = vt * NV;
+  const int lane0 = threadIdx.x;
   int t0, t1;
   if (cu) {
     t0 = min(max(cu[n], 0), T_total);
@@ -183,168 +360,207 @@ __global__ __launch_bounds__(NT) void k_rec_fwd(
     t0 = n * T;
     t1 = t0 + T;
   }
-  float s[RPT][CPL];
-#pragma unroll
-  for (int i = 0; i < RPT; ++i) {
-    const int row = rb * R + grp + i * NG;
-#pragma unroll
-    for (int j = 0; j < CPL; j += 4) {
-      f4 x = zero4();
-      if (S0 && row < DV) x = *(const f4*)(S0 + ((size_t)u * DV + row) * DK + c0 + j);
-      s[i][j] = x[0]; s[i][j + 1] = x[1]; s[i][j + 2] = x[2]; s[i][j + 3] = x[3];
-    }
-  }
 
-  // staging registers of one block
-  u32x4 rq[QKT], rk[QKT], rv[VT];
+  // block loads one block ahead: registers, then LDS.  Tokens past the end
+  // re-read the last one and value rows past DV the last piece (no branches
+  // around the loads): beta = 0 and alpha = 1 there, so nothing of them reaches
+  // the state or a stored output.
+  u32x4 rq[QKN], rk[QKN], rv[VN];
   float rg = 0.f;
-  auto load_block = [&](int tb) {
+  auto load_block = [&](int tb, int lane) {
+    const int g = lane >> 4, m = lane & 15;
+    const float* const gsrc = g == 1 && lam ? lam : g == 2 && la ? la : beta;
 #pragma unroll
-    for (int j = 0; j < QKT; ++j) {
-      const int idx = tid + j * NT;
-      rq[j] = u32x4{0, 0, 0, 0};
-      rk[j] = u32x4{0, 0, 0, 0};
-      const int t = tb + idx / (DK / EPP);
-      if (idx < QKP && t < t1) {
-        const size_t off = ((size_t)t * H + h) * DK + (size_t)(idx % (DK / EPP)) * EPP;
-        rq[j] = *(const u32x4*)(q + off);
-        rk[j] = *(const u32x4*)(k + off);
-      }
+    for (int j = 0; j < QKN; ++j) {
+      const int idx = lane + j * 64, t = min(tb + idx / (DK / EPP), t1 - 1);
+      const size_t off = ((size_t)t * H + h) * DK + (size_t)(idx % (DK / EPP)) * EPP;
+      rq[j] = *(const u32x4*)(q + off);
+      rk[j] = *(const u32x4*)(k + off);
     }
 #pragma unroll
-    for (int j = 0; j < VT; ++j) {
-      const int idx = tid + j * NT;
-      rv[j] = u32x4{0, 0, 0, 0};
-      const int t = tb + idx / (R / EPP);
-      const int row = rb * R + (idx % (R / EPP)) * EPP;   // DV is a multiple of 8: a piece is all in or all out
-      if (idx < VP && t < t1 && row < DV) rv[j] = *(const u32x4*)(v + ((size_t)t * H + h) * DV + row);
+    for (int j = 0; j < VN; ++j) {
+      const int idx = lane + j * 64, t = min(tb + (idx / (NV / EPP)) % RTB, t1 - 1);
+      const int row = min(v0 + (idx % (NV / EPP)) * EPP, DV - EPP);   // DV is a multiple of 8
+      rv[j] = *(const u32x4*)(v + ((size_t)t * H + h) * DV + row);
     }
-    rg = 0.f;
-    if (tid < 3 * TB) {
-      const int which = tid / TB, t = tb + tid % TB;
-      const float* src = which == 0 ? beta : which == 1 ? lam : la;
-      if (src && t < t1) rg = src[(size_t)t * H + h];
-      else if (which == 1 && t < t1) rg = lam_c;           // constant lambda
-    }
+    rg = gsrc[(size_t)min(tb + m, t1 - 1) * H + h];
   };
-  auto store_block = [&](int buf) {
+  auto store_block = [&](int tb, int lane) {
+    const int g = lane >> 4, m = lane & 15;
 #pragma unroll
-    for (int j = 0; j < QKT; ++j) {
-      const int idx = tid + j * NT;
-      if (idx < QKP) {
-        *(u32x4*)(&qs[buf][idx * EPP]) = rq[j];
-        *(u32x4*)(&ks[buf][idx * EPP]) = rk[j];
-      }
+    for (int j = 0; j < QKN; ++j) {
+      const int idx = lane + j * 64, r = idx / (DK / EPP), c = (idx % (DK / EPP)) * EPP;
+      *(u32x4*)(qs + r * LDK + c) = rq[j];
+      *(u32x4*)&sm.k[r][c] = rk[j];
     }
 #pragma unroll
-    for (int j = 0; j < VT; ++j) {
-      const int idx = tid + j * NT;
-      if (idx < VP) *(u32x4*)(&vs[buf][idx * EPP]) = rv[j];
+    for (int j = 0; j < VN; ++j) {
+      const int idx = lane + j * 64;
+      if (idx < VP) *(u32x4*)(&sm.v[0][0] + idx * EPP) = rv[j];
     }
-    if (tid < 3 * TB) gs[buf][tid] = rg;
+    const bool in = tb + m < t1;
+    const float x = g == 0 ? (in ? rg : 0.f) : g == 1 ? (lam ? rg : lam_c) : (in && la ? __expf(rg) : 1.f);
+    sm.gate[g][m] = x;                         // (row 3 is not read)
   };
 
-  float sc = 1.f;                              // true state = sc * s
-  const int nblk = (t1 - t0 + TB - 1) / TB;
-  if (nblk > 0) {
-    load_block(t0);
-    store_block(0);
+  const int nblk = (t1 - t0 + RTB - 1) / RTB;
+  if (nblk > 0) load_block(t0, lane0);
+  // S^T tiles: s[kt][vb][j] = S[v0 + 16 vb + m][rec_col(kt, 4 g + j)]
+  f4 s[NKT][VB];
+  if (S0) {
+#pragma unroll
+    for (int vb = 0; vb < VB; ++vb) {
+      const float* src = S0 + ((size_t)u * DV + min(v0 + 16 * vb + (lane0 & 15), DV - 1)) * DK + 8 * (lane0 >> 4);
+#pragma unroll
+      for (int kt = 0; kt < NKT; ++kt) s[kt][vb] = *(const f4*)(src + 32 * (kt >> 1) + 4 * (kt & 1));
+    }
+  } else {
+#pragma unroll
+    for (int vb = 0; vb < VB; ++vb)
+#pragma unroll
+      for (int kt = 0; kt < NKT; ++kt) s[kt][vb] = zero4();
   }
-  __syncthreads();
   for (int b = 0; b < nblk; ++b) {
-    const int buf = b & 1;
-    const int tb = t0 + b * TB;
-    const int nt = min(TB, t1 - tb);
-    if (b + 1 < nblk) load_block(tb + TB);
-    for (int tt = 0; tt < nt; ++tt) {
-      float qv[CPL], kv[CPL];
-      const float bt = gs[buf][tt], lm = gs[buf][TB + tt];
-      const float al = la ? __expf(gs[buf][2 * TB + tt]) : 1.f;
+    const int tb = t0 + b * RTB, nt = min(RTB, t1 - tb);
+    int lane = lane0;                          // laundered: addresses formed per block, not kept in registers
+    asm volatile("" : "+v"(lane));
+    const int g = lane >> 4, m = lane & 15;
+    store_block(tb, lane);
+    __syncthreads();
+    // rows t = 4 g + j, columns i = m of K K^T and Q K^T; rows t, value columns of K S^T and Q S^T
+    f4 kk = zero4(), qk = zero4(), sk[VB], sq[VB];
 #pragma unroll
-      for (int j = 0; j < CPL; ++j) {
-        qv[j] = tof(qs[buf][tt * DK + c0 + j]);
-        kv[j] = tof(ks[buf][tt * DK + c0 + j]);
+    for (int vb = 0; vb < VB; ++vb) sk[vb] = sq[vb] = zero4();
+#pragma unroll
+    for (int p = 0; p < NKT / 2; ++p) {
+      REC_FENCE;
+      f4 ka[2], qa[2];
+      rec_row8<E>(&sm.k[m][32 * p + 8 * g], ka[0], ka[1]);
+      rec_row8<E>(qs + m * LDK + 32 * p + 8 * g, qa[0], qa[1]);
+      if constexpr (sizeof(E) == 2) {          // products of bf16 inputs are exact in fp32
+        const bf8 kr = *(const bf8*)&sm.k[m][32 * p + 8 * g], qr = *(const bf8*)(qs + m * LDK + 32 * p + 8 * g);
+        kk = Mma<E>::mma(kr, kr, kk);
+        qk = Mma<E>::mma(qr, kr, qk);
       }
-      // S_{t-1} k and S_{t-1} q of the stored rows (true state = sc * stored)
-      float pk[RPT], pq[RPT], vr[RPT];
 #pragma unroll
-      for (int i = 0; i < RPT; ++i) {
-        float a0 = 0.f, a1 = 0.f, b0 = 0.f, b1 = 0.f;
+      for (int hh = 0; hh < 2; ++hh)
 #pragma unroll
-        for (int j = 0; j < CPL; j += 2) {
-          a0 += s[i][j] * kv[j];
-          a1 += s[i][j + 1] * kv[j + 1];
-          b0 += s[i][j] * qv[j];
-          b1 += s[i][j + 1] * qv[j + 1];
+        for (int j = 0; j < 4; ++j) {
+          if constexpr (sizeof(E) == 4) {
+            kk = __builtin_amdgcn_mfma_f32_16x16x4f32(ka[hh][j], ka[hh][j], kk, 0, 0, 0);
+            qk = __builtin_amdgcn_mfma_f32_16x16x4f32(qa[hh][j], ka[hh][j], qk, 0, 0, 0);
+          }
+#pragma unroll
+          for (int vb = 0; vb < VB; ++vb) {
+            sk[vb] = __builtin_amdgcn_mfma_f32_16x16x4f32(ka[hh][j], s[2 * p + hh][vb][j], sk[vb], 0, 0, 0);
+            sq[vb] = __builtin_amdgcn_mfma_f32_16x16x4f32(qa[hh][j], s[2 * p + hh][vb][j], sq[vb], 0, 0, 0);
+          }
         }
-        pk[i] = a0 + a1;
-        pq[i] = b0 + b1;
-        vr[i] = tof(vs[buf][tt * R + grp + i * NG]);
-      }
-      float kq = 0.f;
+    }
+    // decay products for t = 4 g + j: gam = alpha_{m+1}..alpha_t, ge = alpha_0..alpha_t, gb = alpha_{t+1}..alpha_15
+    f4 gam = {1.f, 1.f, 1.f, 1.f}, ge = gam, gb = gam;
+    float gC = 1.f;
+    if (la) {
+      float al[RTB], pm = 1.f, suf = 1.f;
 #pragma unroll
-      for (int j = 0; j < CPL; ++j) kq += kv[j] * qv[j];
-      kq = group8_sum(kq);
+      for (int t = 0; t < RTB; t += 4) *(f4*)&al[t] = *(const f4*)&sm.gate[2][t];
 #pragma unroll
-      for (int i = 0; i < RPT; ++i) {
-        pk[i] = group8_sum(pk[i]);
-        pq[i] = group8_sum(pq[i]);
-      }
-      // S_t = alpha S_{t-1} + e k^T with e = beta (v - alpha S_{t-1} x), x = k + lambda q,
-      // and o_t = S_t q = alpha S_{t-1} q + e (k . q)
-      float oq[RPT], ev[RPT];
-#pragma unroll
-      for (int i = 0; i < RPT; ++i) {
-        const float sq = sc * pq[i];
-        const float e = bt * (vr[i] - al * (sc * pk[i] + lm * sq));
-        oq[i] = al * sq + e * kq;
-        ev[i] = e;
-      }
-      if (al >= 0x1p-6f) {               // decay folded into the scale: one FMA per element
-        sc *= al;
-        const float rs = 1.f / sc;
-#pragma unroll
-        for (int i = 0; i < RPT; ++i) {
-          const float g = ev[i] * rs;
-#pragma unroll
-          for (int j = 0; j < CPL; ++j) s[i][j] += g * kv[j];
+      for (int t = 0; t < RTB; ++t) {
+        gC *= al[t];
+        pm = t > m ? pm * al[t] : 1.f;
+        if (t >> 2 == g) {
+          gam[t & 3] = pm;
+          ge[t & 3] = gC;
         }
-      } else {                           // strong decay: explicit update, scale reset
-        const float f = sc * al;
-#pragma unroll
-        for (int i = 0; i < RPT; ++i)
-#pragma unroll
-          for (int j = 0; j < CPL; ++j) s[i][j] = f * s[i][j] + ev[i] * kv[j];
-        sc = 1.f;
       }
-      if ((tid % LPR) == 0) {
-        const size_t r = ((size_t)(tb + tt) * H + h) * DV;
 #pragma unroll
-        for (int i = 0; i < RPT; ++i) {
-          const int row = rb * R + grp + i * NG;
-          if (row < DV) o[r + row] = fromf<E>(oq[i]);
-        }
+      for (int t = RTB - 1; t >= 0; --t) {
+        if (t >> 2 == g) gb[t & 3] = suf;
+        suf *= al[t];
       }
     }
-    // fold the scale back in once per block: it stays >= 2^-96 (16 tokens of
-    // alpha >= 2^-6), inside the normal fp32 range
+    const f4 be = *(const f4*)&sm.gate[0][4 * g], lm = *(const f4*)&sm.gate[1][4 * g];
+    __syncthreads();                           // Q consumed: its room takes g_t S q_t
 #pragma unroll
-    for (int i = 0; i < RPT; ++i)
+    for (int j = 0; j < 4; ++j) {
+      const int t = 4 * g + j;
+      const bool in = t < nt;                  // no e past the end, whatever the repeated token holds
+      sm.A[t][m] = in ? be[j] * gam[j] * (kk[j] + lm[j] * qk[j]) : 0.f;   // (right of the diagonal: not read)
+      sm.Pm[t][m] = gam[j] * qk[j];
 #pragma unroll
-      for (int j = 0; j < CPL; ++j) s[i][j] *= sc;
-    sc = 1.f;
-    if (b + 1 < nblk) store_block(buf ^ 1);   // the buffer read in block b - 1
+      for (int vb = 0; vb < VB; ++vb) {
+        const float sqg = ge[j] * sq[vb][j];
+        const float x = be[j] * (tof(sm.v[t][16 * vb + m]) - (ge[j] * sk[vb][j] + lm[j] * sqg));
+        sm.x[t][16 * vb + m] = in ? x : 0.f;
+        xq[t * LDX + 16 * vb + m] = sqg;
+      }
+    }
     __syncthreads();
+    {
+      // one value row per lane (with fewer rows than lanes the upper lanes
+      // repeat the lower ones' work)
+      const int r = lane % NV, row = v0 + r;
+      float e[RTB], y[RTB];
+#pragma unroll
+      for (int t = 0; t < RTB; ++t) {
+        REC_FENCE;
+        float x0 = sm.x[t][r], x1 = 0.f, y0 = xq[t * LDX + r], y1 = 0.f;
+#pragma unroll
+        for (int i = 0; i < t; i += 4) {
+          const f4 ac = *(const f4*)&sm.A[t][i], pc = *(const f4*)&sm.Pm[t][i];
+#pragma unroll
+          for (int j = 0; j < 4; ++j)
+            if (i + j < t) {
+              (j & 1 ? x1 : x0) -= ac[j] * e[i + j];
+              (j & 1 ? y1 : y0) += pc[j] * e[i + j];
+            }
+        }
+        e[t] = x0 + x1;
+        y[t] = y0 + sm.Pm[t][t] * e[t] + y1;
+        asm volatile("" : "+v"(y[t]));         // formed here: sunk into the stores' branch it would hold every row of Pm
+      }
+      if (lane < NV && row < DV) {
+        E* op = o + ((size_t)tb * H + h) * DV + row;
+#pragma unroll
+        for (int t = 0; t < RTB; ++t) {
+          if (t < nt) *op = fromf<E>(y[t]);
+          op += (size_t)H * DV;
+        }
+      }
+#pragma unroll
+      for (int t = 0; t < RTB; ++t)
+        if (lane < NV) sm.x[t][r] = e[t];
+    }
+    __syncthreads();
+    if (b + 1 < nblk) load_block(tb + RTB, lane);   // lands during the update
+    // S^T <- g_C S^T + K^T diag(Gam_C) e
+    f4 eb[VB];
+#pragma unroll
+    for (int vb = 0; vb < VB; ++vb)
+#pragma unroll
+      for (int j = 0; j < 4; ++j) eb[vb][j] = gb[j] * sm.x[4 * g + j][16 * vb + m];
+#pragma unroll
+    for (int kt = 0; kt < NKT; ++kt) {
+      if (kt % 2 == 0) REC_FENCE;
+      const f4 kt4 = rec_tok4<E>(&sm.k[0][0], LDK, kt, lane);
+#pragma unroll
+      for (int vb = 0; vb < VB; ++vb) {
+        f4 a = gC * s[kt][vb];
+#pragma unroll
+        for (int j = 0; j < 4; ++j) a = __builtin_amdgcn_mfma_f32_16x16x4f32(kt4[j], eb[vb][j], a, 0, 0, 0);
+        s[kt][vb] = a;
+      }
+    }
+    __syncthreads();                           // the block's LDS use is over
   }
   if (Sfin) {
 #pragma unroll
-    for (int i = 0; i < RPT; ++i) {
-      const int row = rb * R + grp + i * NG;
+    for (int vb = 0; vb < VB; ++vb) {
+      const int row = v0 + 16 * vb + (lane0 & 15);
       if (row < DV) {
+        float* dst = Sfin + ((size_t)u * DV + row) * DK + 8 * (lane0 >> 4);
 #pragma unroll
-        for (int j = 0; j < CPL; j += 4)
-          *(f4*)(Sfin + ((size_t)u * DV + row) * DK + c0 + j) =
-              f4{s[i][j], s[i][j + 1], s[i][j + 2], s[i][j + 3]};
+        for (int kt = 0; kt < NKT; ++kt) *(f4*)(dst + 32 * (kt >> 1) + 4 * (kt & 1)) = s[kt][vb];
       }
     }
   }
@@ -356,27 +572,42 @@ hipError_t launch_rec_fwd(int N, int T, const int* cu, int T_total, int H, int D
                           const float* S0, float* Sfin, void* o, hipStream_t st) {
   if (N == 0) return hipSuccess;
   if (!((dtype == 1 || dtype == 0) && (Dk == 128 || Dk == 64))) return hipErrorInvalidValue;
-  // 128 threads = 16 lane groups; up to eight rows per group, so one
-  // workgroup holds up to 128 rows of a unit and a single round of
-  // workgroups (two waves per SIMD) covers the whole grid at 64 x 16 units
-  constexpr int NT = 128, NG = NT / 8;
-  const int rpt = Dv > 4 * NG ? 8 : Dv > 2 * NG ? 4 : Dv > NG ? 2 : 1;
-  const int nrb = (Dv + NG * rpt - 1) / (NG * rpt);
-  dim3 grid((unsigned)((size_t)N * H * nrb));
-#define QD_REC(ET, DKV, RPTV)                                                                   \
-  hipLaunchKernelGGL((k_rec_fwd<ET, DKV, RPTV, NT>), grid, dim3(NT), 0, st, T, H, Dv, nrb, cu, \
+  // A few tokens per sequence go through the step kernel: many short waves
+  // with one read and one write of the state overlap better than one round of
+  // long ones, until its row sums cost more.  16 heads, d 128, 64 sequences:
+  // bf16 T = 1 / 2 / 4 / 6: 24 / 28 / 37 / 47 us against 39 in blocks; fp32
+  // T = 4 / 6 / 8: 32 / 40 / 47 against 45; one sequence, T = 4 / 6 / 8: bf16
+  // 6.1 / 8.1 / 10.2 against 7.1, fp32 5.4 / 7.0 / 8.7 against 7.5.  Packed
+  // lengths are not known here: their mean decides, and lower, since one long
+  // sequence would walk alone.
+  if (cu ? T_total <= 2LL * N : T >= 1 && T <= (dtype == 1 ? 4 : 6))
+    return step_at(N, T, cu, T_total, H, Dk, Dv, dtype, q, k, v, beta, lam, lam_c, la, S0, Sfin, o, st);
+  const int units = N * H;
+  // Wide tiles once they are two waves per SIMD or more (bf16; from one per SIMD
+  // on where a sequence has more than two blocks to walk) or half a wave per
+  // SIMD (fp32), 16-row tiles below: there a wave's own chain of products is
+  // the time.  16 heads, d 128, bf16, T = 16: 64 sequences 40.6 us in 16-row
+  // tiles, 39.5 wide; 32: 23.6, 25.9; 8: 9.8, 14.8; T = 64: 64 sequences 121,
+  // 88; 32: 65, 57; 16: 36, 49.  fp32, T = 16: 16 sequences 20.3, 15.4; 8: 10.8, 12.0.
+  const long long t16 = (long long)units * ((Dv + 15) / 16), cus = device_cu_count();
+  const bool lengthy = (cu ? T_total / N : T) > 2 * RTB;
+  const bool wide = dtype == 1 ? t16 >= 32 * cus || (lengthy && t16 >= 16 * cus) : t16 >= 8 * cus;
+  const int vb = !wide ? 1 : dtype == 1 && Dk == 128 ? rec_wide<__bf16, 128>() : 2;
+  const int ntile = (Dv + 16 * vb - 1) / (16 * vb);
+  dim3 grid((unsigned)((size_t)(units + 7) / 8 * 8 * ntile));
+#define QD_REC(ET, DKV, VBV)                                                                        \
+  hipLaunchKernelGGL((k_rec_fwd<ET, DKV, VBV>), grid, dim3(64), 0, st, T, H, Dv, units, ntile, cu, \
                      T_total, (const ET*)q, (const ET*)k, (const ET*)v, beta, lam, lam_c, la,  \
                      S0, Sfin, (ET*)o)
-#define QD_REC_R(ET, DKV)                                                    \
-  if (rpt == 8) QD_REC(ET, DKV, 8); else if (rpt == 4) QD_REC(ET, DKV, 4);   \
-  else if (rpt == 2) QD_REC(ET, DKV, 2); else QD_REC(ET, DKV, 1)
+#define QD_REC_V(ET, DKV) \
+  if (wide) QD_REC(ET, DKV, (rec_wide<ET, DKV>())); else QD_REC(ET, DKV, 1)
   prof_mark(ST_REC_FWD, 0, st);
-  if (dtype == 1 && Dk == 128) { QD_REC_R(__bf16, 128); }
-  else if (dtype == 1 && Dk == 64) { QD_REC_R(__bf16, 64); }
-  else if (dtype == 0 && Dk == 128) { QD_REC_R(float, 128); }
-  else { QD_REC_R(float, 64); }
+  if (dtype == 1 && Dk == 128) { QD_REC_V(__bf16, 128); }
+  else if (dtype == 1 && Dk == 64) { QD_REC_V(__bf16, 64); }
+  else if (dtype == 0 && Dk == 128) { QD_REC_V(float, 128); }
+  else { QD_REC_V(float, 64); }
   prof_mark(ST_REC_FWD, 1, st);
-#undef QD_REC_R
+#undef QD_REC_V
 #undef QD_REC
   return hipGetLastError();
 }

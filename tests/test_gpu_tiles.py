@@ -1,10 +1,11 @@
 """GPU parity where the launch rules change the tile width: unit counts on both sides of each line, ragged lengths,
 forward and backward against the fp64 oracle (sampled heads; normwise tolerances as everywhere)."""
+import numpy as np
 import pytest
 import torch
 
-from paper_2606_08804_amd import synth
-from tests.gpu_helpers import TOL, bwd_errors, fwd_errors, gpu_bwd, gpu_fwd, select_heads
+from paper_2606_08804_amd import qdelta, synth
+from tests.gpu_helpers import TOL, bwd_errors, dev, fwd_errors, gpu_bwd, gpu_fwd, select_heads
 
 pytestmark = pytest.mark.gpu
 
@@ -21,3 +22,56 @@ def test_fp32_scan_tile_widths(H, Dv):
     g = {k: v[:, heads] if k == "d_initial_state" else v[:, :, heads] for k, v in g.items()}
     errs = {**fwd_errors(ds, o, Sf), **bwd_errors(ds, g)}
     assert all(v <= TOL["f32"] for v in errs.values()), errs
+
+
+def _rec(d):
+    return qdelta.recurrent_fwd(dev(d["q"]), dev(d["k"]), dev(d["v"]), dev(d["beta"]), dev(d["lam"]),
+                                dev(d["log_alpha"]), dev(d["initial_state"]), cu_seqlens=dev(d["cu_seqlens"]))
+
+
+# fp32 state arithmetic: bf16 inputs add only the rounding of o (2^-9 of a value)
+REC_TOL = {"f32": 5e-6, "bf16": 4e-3}
+
+
+@pytest.mark.parametrize("dt,Dk,Dv", [("bf16", 128, 72), ("bf16", 64, 8), ("f32", 128, 40), ("f32", 64, 256)])
+@pytest.mark.parametrize("T", [1, 2, 4, 5, 6, 7, 15, 16, 17, 49])
+def test_recurrent_fwd_lengths(T, dt, Dk, Dv):
+    """Both sides of the step / block rule, block edges, and value rows that no tile divides."""
+    d = synth.make(2, T, 3, Dk, Dv, dt, "G3", seed=720 + T, s0=True)
+    errs = fwd_errors(d, *_rec(d))
+    assert all(v <= REC_TOL[dt] for v in errs.values()), errs
+
+
+@pytest.mark.parametrize("dt,Dk,B,H,T", [("bf16", 128, 64, 16, 18), ("bf16", 128, 33, 16, 33), ("bf16", 64, 64, 16, 18),
+                                         ("f32", 128, 16, 16, 18), ("f32", 64, 15, 17, 18)])
+def test_recurrent_fwd_wide_tiles(dt, Dk, B, H, T):
+    """Unit counts at and beside the wide-tile rule."""
+    d = synth.make(B, T, H, Dk, 128, dt, "G3", seed=741, s0=True)
+    o, Sf = _rec(d)
+    heads = [0, H - 1]
+    errs = fwd_errors(select_heads(d, heads), o[:, :, heads], Sf[:, heads])
+    assert all(v <= REC_TOL[dt] for v in errs.values()), errs
+
+
+@pytest.mark.parametrize("lengths", [[1, 1, 1], [2, 0, 3, 1], [0, 40, 0, 16, 17, 1]])
+def test_recurrent_fwd_packed_routes(lengths):
+    """Packed batches on both sides of the mean-length rule, empty sequences among them."""
+    d = synth.make(1, 0, 2, 128, 64, "f32", "G2", seed=751, lengths=lengths, s0=True)
+    errs = fwd_errors(d, *_rec(d))
+    assert all(v <= REC_TOL["f32"] for v in errs.values()), errs
+
+
+@pytest.mark.parametrize("T", [4, 12, 40])
+def test_recurrent_fwd_is_causal_and_takes_alpha_zero(T):
+    """alpha = 0 (log alpha = -inf) forgets the state exactly; a NaN in one token leaves every earlier output as it was."""
+    d = synth.make(1, T, 2, 64, 64, "f32", "G2", seed=761, s0=True)
+    d["log_alpha"][0, T // 2] = -np.inf
+    o, Sf = _rec(d)
+    errs = fwd_errors(d, o, Sf)
+    assert all(v <= REC_TOL["f32"] for v in errs.values()), errs
+    d2 = {k: v.clone() if isinstance(v, torch.Tensor) else v for k, v in d.items()}
+    at = T // 2 + 1
+    for key in ("q", "k", "v", "beta"):
+        d2[key][0, at] = float("nan")
+    o2, _ = _rec(d2)
+    assert torch.equal(o2[:, :at], o[:, :at]) and not torch.isfinite(o2[:, at]).any()
