@@ -657,12 +657,10 @@ static int rec_bwd_impl(bool varlen, int32_t B, int32_t T, int32_t N, const int3
   a.dq = dq; a.dk = dk; a.dv = dv;
   a.dbeta = dbeta; a.dla = dlog_alpha; a.dS0 = d_initial_state;
   a.dlam = dlam_const ? nullptr : dlam;
-  size_t off = 0;
-  a.wP = reinterpret_cast<float*>(w + off); off += r(tok * H * Dv * 4);
-  a.wZ = reinterpret_cast<float*>(w + off); off += r(tok * H * Dv * 4);
-  a.wDP = reinterpret_cast<float*>(w + off); off += r(tok * H * Dv * 4);
-  a.wWK = reinterpret_cast<float*>(w + off); off += r(tok * H * Dk * 4);
-  a.wF = reinterpret_cast<float*>(w + off); off += r((size_t)n_seqs * H * Dv * 4);
+  // stored entry states, at most one per 16 rec_ckpt tokens and head, then the
+  // per-token gradients of a constant lambda
+  a.wS = reinterpret_cast<float*>(w);
+  const size_t off = 3 * r(tok * H * Dv * 4) + r(tok * H * Dk * 4) + r((size_t)n_seqs * H * Dv * 4);
   a.wDL = dlam_const ? reinterpret_cast<float*>(w + off) : nullptr;
   hipError_t e = qd::launch_rec_bwd(a, n_seqs * H, dtype, Dk, dlam_const ? dlam : nullptr, (long long)tok * H,
                                     stream);

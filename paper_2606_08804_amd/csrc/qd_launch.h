@@ -57,6 +57,16 @@ hipError_t launch_rec_fwd(int N, int T, const int* cu, int T_total, int H, int D
                           const float* beta, const float* lam, float lam_c, const float* la,
                           const float* S0, float* Sfin, void* o, hipStream_t st);
 
+// The recurrent backward stores the entry state of every rec_ckpt-th block of
+// 16 tokens.  The workspace holds 3 Dv + Dk floats per token and head
+// (qdelta_recurrent_workspace_bytes), so the spacing is the smallest whose
+// states fit: 2, or 3 at Dk = 128 with Dv = 256.
+__host__ __device__ constexpr int rec_ckpt(int Dk, int Dv) {
+  int c = 1;
+  while (16 * c * (3 * Dv + Dk) < Dv * Dk) ++c;
+  return c;
+}
+
 // Arguments of the fully recurrent backward (one workgroup per (sequence,
 // head) unit).
 struct RecBwdArgs {
@@ -70,7 +80,7 @@ struct RecBwdArgs {
   void *dq, *dk, *dv;
   float *dbeta, *dlam, *dla, *dS0;
   float* wDL;               // per token-head gradient of a constant lambda (else nullptr)
-  float *wP, *wZ, *wDP, *wWK, *wF;   // workspace: [tok][H][DV] x3 and [tok][H][DK] fp32, [unit][DV] fp32
+  float* wS;                // workspace: stored entry states, [slot][H][DV][DK] fp32 (rec_ckpt)
 };
 
 // Fully recurrent backward over `units` (sequence, head) units; when

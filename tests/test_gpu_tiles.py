@@ -75,3 +75,49 @@ def test_recurrent_fwd_is_causal_and_takes_alpha_zero(T):
         d2[key][0, at] = float("nan")
     o2, _ = _rec(d2)
     assert torch.equal(o2[:, :at], o[:, :at]) and not torch.isfinite(o2[:, at]).any()
+
+
+def _rec_bwd(d, dsf, need=True):
+    return qdelta.recurrent_bwd(dev(d["q"]), dev(d["k"]), dev(d["v"]), dev(d["beta"]), dev(d["lam"]),
+                                dev(d["log_alpha"]), dev(d["initial_state"]), dev(d["d_o"]), d_final_state=dev(dsf),
+                                cu_seqlens=dev(d["cu_seqlens"]), need_d_initial_state=need)
+
+
+def _dsf(d, N):
+    H, Dv, Dk = d["v"].shape[2], d["v"].shape[3], d["q"].shape[3]
+    return torch.from_numpy(np.random.default_rng(5).standard_normal((N, H, Dv, Dk)).astype(np.float32))
+
+
+@pytest.mark.parametrize("dt,Dk,Dv", [("bf16", 128, 128), ("f32", 128, 256), ("f32", 64, 32), ("bf16", 64, 64)])
+@pytest.mark.parametrize("T", [3, 15, 16, 17, 32, 33, 49, 97])
+def test_recurrent_bwd_lengths(T, dt, Dk, Dv):
+    """One block and several, on and beside the block edges and the spacing of the stored states (2 or 3 blocks),
+    with a final-state gradient; alpha = 0 in one token.  fp32 sums: 1e-5 of the largest value."""
+    d = synth.make(2, T, 3, Dk, Dv, dt, "G3", seed=770 + T, s0=True, with_do=True)
+    d["log_alpha"][1, T // 2] = -np.inf
+    dsf = _dsf(d, 2)
+    errs = bwd_errors(d, _rec_bwd(d, dsf), dsf)
+    tol = 1e-5 if dt == "f32" else REC_TOL[dt]
+    assert all(v <= tol for v in errs.values()), errs
+
+
+@pytest.mark.parametrize("lengths", [[16, 0, 17, 1, 33, 50, 15], [40, 31, 32, 33, 1, 64]])
+def test_recurrent_bwd_packed_stored_states(lengths):
+    """The stored states of packed sequences that start anywhere within a block do not overlap."""
+    d = synth.make(1, 0, 2, 64, 64, "f32", "G2", seed=781, lengths=lengths, s0=True, with_do=True)
+    dsf = _dsf(d, len(lengths))
+    errs = bwd_errors(d, _rec_bwd(d, dsf), dsf)
+    assert all(v <= 1e-5 for v in errs.values()), errs
+
+
+@pytest.mark.parametrize("T", [5, 40])
+def test_recurrent_bwd_without_state_gradients(T):
+    """No initial state, no final-state gradient, no initial-state gradient wanted: the same token gradients."""
+    d = synth.make(2, T, 2, 128, 64, "f32", "G1", seed=791, with_do=True)
+    full = _rec_bwd(d, None)
+    part = _rec_bwd(d, None, need=False)
+    assert part["d_initial_state"] is None
+    for key in ("dq", "dk", "dv", "dbeta", "dlam"):
+        assert torch.equal(full[key], part[key]), key
+    errs = bwd_errors(d, part, skip=("d_initial_state",))
+    assert all(v <= 1e-5 for v in errs.values()), errs
