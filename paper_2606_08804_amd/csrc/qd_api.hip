@@ -9,6 +9,7 @@
 
 #include "qd_launch.h"
 #include "qdelta.h"
+#include "qdelta_layer.h"
 
 namespace {
 
@@ -156,7 +157,7 @@ int fwd_impl(bool varlen, int32_t B, int32_t T, int32_t N, const int32_t* cu, in
              int32_t Dk, int32_t Dv, int32_t chunk, int32_t dtype, const void* q, const void* k,
              const void* v, const float* beta, const float* lam, float lam_c, const float* log_alpha,
              const float* initial_state, void* o, float* final_state, void* saved,
-             void* ws, size_t ws_bytes, hipStream_t stream, bool dry = false) {
+             void* ws, size_t ws_bytes, hipStream_t stream, bool dry = false, int32_t ldv = 0) {
   Sizes s;
   int rc = make_sizes(varlen, B, T, N, cu, s);
   if (rc) return rc;
@@ -182,7 +183,7 @@ int fwd_impl(bool varlen, int32_t B, int32_t T, int32_t N, const int32_t* cu, in
   p.NT = varlen ? 0 : (s.T + C - 1) / C;
   p.n_slots = (int)s.slots;
   p.cu = s.cu;
-  p.q = q; p.k = k; p.v = v;
+  p.q = q; p.k = k; p.v = v; p.ldv = ldv ? ldv : Dv;
   p.beta = beta; p.lam = lam; p.lam_c = lam_c; p.la = log_alpha; p.S0 = initial_state;
   p.o = has_tokens ? o : nullptr;
   p.Sfin = final_state;
@@ -206,7 +207,8 @@ int bwd_impl(bool varlen, int32_t B, int32_t T, int32_t N, const int32_t* cu, in
              const float* initial_state, const void* saved, const void* d_o,
              const float* d_final_state, void* dq, void* dk, void* dv, float* dbeta, float* dlam,
              float* dlog_alpha, float* d_initial_state, void* ws, size_t ws_bytes,
-             hipStream_t stream) {
+             hipStream_t stream, int32_t ldv = 0, int32_t ldd = 0, const float* rnq = nullptr,
+             const float* rnk = nullptr) {
   Sizes s;
   int rc = make_sizes(varlen, B, T, N, cu, s);
   if (rc) return rc;
@@ -245,7 +247,10 @@ int bwd_impl(bool varlen, int32_t B, int32_t T, int32_t N, const int32_t* cu, in
   p.NT = varlen ? 0 : (s.T + C - 1) / C;
   p.n_slots = (int)s.slots;
   p.cu = s.cu;
-  p.q = q; p.k = k; p.v = v;
+  p.q = q; p.k = k; p.v = v; p.ldv = ldv ? ldv : Dv;
+  p.ldqk = ldd ? ldd : Dk;
+  p.lddv = ldd ? ldd : Dv;
+  p.rnq = rnq; p.rnk = rnk;
   p.beta = beta; p.lam = lam; p.lam_c = lam_c; p.la = log_alpha; p.S0 = initial_state;
   p.dO = d_o;
   p.dSfin = d_final_state;
@@ -491,7 +496,7 @@ int qdelta_chunk_fwd_segmented(int32_t B, int32_t T, int32_t H, int32_t Dk, int3
   p.NT = NT;
   p.n_slots = (int)slots;
   p.cu = nullptr;
-  p.q = q; p.k = k; p.v = v;
+  p.q = q; p.k = k; p.v = v; p.ldv = Dv;
   p.beta = beta; p.lam = lam; p.lam_c = lam_scalar; p.la = log_alpha; p.S0 = initial_state;
   p.o = T > 0 ? o : nullptr;
   p.Sfin = final_state;
@@ -715,6 +720,47 @@ int qdelta_l2norm_bwd(int64_t rows, int32_t D, int32_t dtype, const void* y, con
   if (!(ok_ptr(y) && ok_ptr(rnorm) && ok_ptr(dy) && ok_ptr(dx))) return QDELTA_EINVAL;
   hipError_t e = qd::launch_l2norm(1, rows, D, D, dtype, nullptr, y, rnorm, nullptr, dy, dx, stream);
   return e == hipSuccess ? QDELTA_OK : QDELTA_EHIP;
+}
+
+int qdelta_layer_fwd(int32_t B, int32_t T, int32_t N, const int32_t* cu_seqlens, int32_t H, int32_t Dk, int32_t Dv,
+                     int32_t dtype, const void* qkv, const float* beta, const float* lam, float lam_scalar,
+                     const float* log_alpha, const float* initial_state, void* q, void* k, float* rnorm_q,
+                     float* rnorm_k, void* o, float* final_state, void* saved, void* ws, size_t ws_bytes,
+                     hipStream_t stream) {
+  const bool varlen = cu_seqlens != nullptr;
+  const int esz = dtype == QDELTA_BF16 ? 2 : 4;
+  const int32_t ld = 2 * Dk + Dv;
+  const char* x = static_cast<const char*>(qkv);
+  if (!ok_ptr(qkv) || !ok_ptr(rnorm_q) || !ok_ptr(rnorm_k)) return QDELTA_EINVAL;
+  // everything is validated before the first launch
+  auto core = [&](bool dry) {
+    return fwd_impl(varlen, B, T, varlen ? N : B, cu_seqlens, H, Dk, Dv, C, dtype, q, k, x + (size_t)2 * Dk * esz, beta,
+                    lam, lam_scalar, log_alpha, initial_state, o, final_state, saved, ws, ws_bytes, stream, dry, ld);
+  };
+  int rc = core(true);
+  if (rc != QDELTA_OK) return rc;
+  const long rows = (varlen ? (long)T : (long)B * T) * H;
+  if (qd::launch_l2norm2(rows, Dk, ld, dtype, x, q, rnorm_q, x + (size_t)Dk * esz, k, rnorm_k, stream) != hipSuccess)
+    return QDELTA_EHIP;
+  return core(false);
+}
+
+int qdelta_layer_bwd(int32_t B, int32_t T, int32_t N, const int32_t* cu_seqlens, int32_t H, int32_t Dk, int32_t Dv,
+                     int32_t dtype, const void* qkv, const void* q, const void* k, const float* rnorm_q,
+                     const float* rnorm_k, const float* beta, const float* lam, float lam_scalar,
+                     const float* log_alpha, const float* initial_state, const void* saved, const void* d_o,
+                     const float* d_final_state, void* dqkv, float* dbeta, float* dlam, float* dlog_alpha,
+                     float* d_initial_state, void* ws, size_t ws_bytes, hipStream_t stream) {
+  const bool varlen = cu_seqlens != nullptr;
+  const int esz = dtype == QDELTA_BF16 ? 2 : 4;
+  const int32_t ld = 2 * Dk + Dv;
+  if (!ok_ptr(qkv) || !ok_ptr(dqkv) || !ok_ptr(rnorm_q) || !ok_ptr(rnorm_k) || !ok_ptr(saved)) return QDELTA_EINVAL;
+  const char* x = static_cast<const char*>(qkv);
+  char* d = static_cast<char*>(dqkv);
+  return bwd_impl(varlen, B, T, varlen ? N : B, cu_seqlens, H, Dk, Dv, C, dtype, q, k, x + (size_t)2 * Dk * esz, beta,
+                  lam, lam_scalar, log_alpha, initial_state, saved, d_o, d_final_state, d, d + (size_t)Dk * esz,
+                  d + (size_t)2 * Dk * esz, dbeta, dlam, dlog_alpha, d_initial_state, ws, ws_bytes, stream, ld, ld,
+                  rnorm_q, rnorm_k);
 }
 
 int qdelta_recurrent_step(int32_t N, int32_t H, int32_t Dk, int32_t Dv, int32_t dtype,

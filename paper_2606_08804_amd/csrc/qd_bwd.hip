@@ -286,7 +286,7 @@ __global__ __launch_bounds__(NCW * 64 + 256) void k_scan_bwd(Params p) {
       // and z1 = g_r (dO - lambda_r dV), z2 = -g_r dV are formed here, where
       // the wave's own rows cover the tile once.
       const float betar = gb[C + rr], gr = __expf(gb[rr]), lr = gb[2 * C + rr];
-      E* vrow = (E*)p.dv + ((size_t)(t0 + rr) * H + h) * DV + v0;
+      E* vrow = (E*)p.dv + ((size_t)(t0 + rr) * H + h) * p.lddv + v0;
 #pragma unroll
       for (int jn = 0; jn < NBW; ++jn) {
         const int nb = nb0 + jn;
@@ -436,7 +436,10 @@ constexpr int INTRA_THREADS = NTHREADS;
 template <typename E>
 constexpr int intra_per_cu() { return sizeof(E) == 2 ? 2 : 1; }
 
-template <typename E, int DK, int DV>
+// NORM: q and k are L2-normalised rows; the kernel applies the backward of the
+// normalisation to its dq and dk while it holds them (a pass of its own over
+// them reads and writes 4 x 67 MB at B4 T4096 H16 d128, and took 71 us).
+template <typename E, int DK, int DV, bool NORM>
 __global__ __launch_bounds__(INTRA_THREADS) __attribute__((amdgpu_waves_per_eu(intra_per_cu<E>(), intra_per_cu<E>()))) void k_bwd_intra(Params p) {
   constexpr int KS = Mma<E>::KS;
   constexpr int NKB = DK / 16;        // 16-column blocks of Dk
@@ -498,7 +501,7 @@ __global__ __launch_bounds__(INTRA_THREADS) __attribute__((amdgpu_waves_per_eu(i
   const char* dSg = (const char*)((const E*)p.w_dSo + gi * DK * DV);
   const char* Dg = (const char*)((const E*)p.savedD + gi * C * DV);   // 32-column tiles, C x 32 each
   const char* dOg = (const char*)((const E*)p.dO + arow * DV);
-  const char* Vg = (const char*)((const E*)p.v + arow * DV);
+  const char* Vg = (const char*)((const E*)p.v + arow * p.ldv);
   // the gate block (b, beta, lambda; waves 0-2 one vector each, straight
   // into LDS) and this wave's rows of K as B operands of Kbar dS'^T (k = key;
   // rows past the chunk re-read its last row: their dD rows are zeroed),
@@ -520,7 +523,7 @@ __global__ __launch_bounds__(INTRA_THREADS) __attribute__((amdgpu_waves_per_eu(i
     dma_rows<RK, BV, NWAVES, true>(t + TA::S, Sg + vb * RK, RK, BV, Sg, 0, w, ln);
     dma_rows<RK, BV, NWAVES, true>(t + TA::DS, dSg + vb * RK, RK, BV, dSg, 0, w, ln);
     dma_rows<TA::RE, C, NWAVES, true>(t + TA::D, Dt, TA::RE, C, Dt, 0, w, ln);
-    dma_rows<TA::RE, C, NWAVES, true>(t + TA::V, Vg + vb * ES, (size_t)H * DV * ES, len, Dt, TA::RE, w, ln);
+    dma_rows<TA::RE, C, NWAVES, true>(t + TA::V, Vg + vb * ES, (size_t)H * p.ldv * ES, len, Dt, TA::RE, w, ln);
     dma_rows<TA::RE, C, NWAVES, true>(t + TA::DO, dOg + vb * ES, (size_t)H * DV * ES, len, Dt, TA::RE, w, ln);
   };
   // this wave's rows of the tile's dD, as their transpose (value rows, chunk
@@ -859,10 +862,20 @@ __global__ __launch_bounds__(INTRA_THREADS) __attribute__((amdgpu_waves_per_eu(i
     }
     const float gr = sm.g[rr], lr = sm.lam[rr], kbr = __expf(sm.b[C - 1] - sm.b[rr]);
     float s1 = 0.f, s2 = 0.f, s3 = 0.f;
-    E* dqo = (E*)p.dq + (arow + (size_t)rr * H) * DK;
-    E* dko = (E*)p.dk + (arow + (size_t)rr * H) * DK;
+    const size_t orow = arow + (size_t)rr * H;
+    E* dqo = (E*)p.dq + orow * p.ldqk;
+    E* dko = (E*)p.dk + orow * p.ldqk;
+    // NORM: 1 / |row| of the rows behind q and k, and y . dy of this row
+    float rq = 0.f, rk = 0.f, yq = 0.f, yk = 0.f;
+    if (NORM && rr < len) {
+      rq = p.rnq[orow];
+      rk = p.rnk[orow];
+    }
 #pragma unroll
     for (int kb = 0; kb < NKB; ++kb) {
+      if constexpr (NORM) {
+        __builtin_amdgcn_sched_barrier(0);   // one block's operands at a time (registers)
+      }
       f4 dxp = zero4(), dqp = zero4(), dkp = zero4();
 #pragma unroll
       for (int ks = 0; ks < NKC; ++ks) {
@@ -888,9 +901,47 @@ __global__ __launch_bounds__(INTRA_THREADS) __attribute__((amdgpu_waves_per_eu(i
         oq[j] = gr * aq + dqp[j] + lr * dX;
         ok[j] = kbr * ak + dkp[j] + dX;
       }
-      if (rr < len) {
+      if constexpr (NORM) {
+#pragma unroll
+        for (int j = 0; j < 4; ++j) {
+          yq += Quad<E>::get(qq, j) * oq[j];
+          yk += Quad<E>::get(kq, j) * ok[j];
+        }
+        aQt[kb] = oq;                      // (its last use was above)
+        aKt[kb] = ok;
+        // the sums formed here, not after the stores below, which would keep every block's terms
+        asm volatile("" : "+v"(s1), "+v"(s2), "+v"(s3), "+v"(yq), "+v"(yk));
+      } else if (rr < len) {
         *(QR*)(dqo + kc) = Quad<E>::pack(oq);
         *(QR*)(dko + kc) = Quad<E>::pack(ok);
+      }
+    }
+    if constexpr (NORM) {
+      // gradients of the rows before the normalisation: r (dy - y (y . dy)), r dy for a clamped row
+      yq += lane_xor(yq, 16, lb);
+      yq += lane_xor(yq, 32, lb);
+      yk += lane_xor(yk, 16, lb);
+      yk += lane_xor(yk, 32, lb);
+      yq = rq > 0.f ? yq : 0.f;
+      yk = rk > 0.f ? yk : 0.f;
+      rq = fabsf(rq);
+      rk = fabsf(rk);
+      if (rr < len) {
+#pragma unroll
+        for (int kb = 0; kb < NKB; ++kb) {
+          __builtin_amdgcn_sched_barrier(0);
+          const int kc = kb * 16 + frow(lb, 0);
+          const QR kq = *(const QR*)(ring + SM::OK + tile_off<RK>(rr, kc * (int)ES));
+          const QR qq = *(const QR*)(ring + SM::OQ + tile_off<RK>(rr, kc * (int)ES));
+          f4 oq, ok;
+#pragma unroll
+          for (int j = 0; j < 4; ++j) {
+            oq[j] = rq * (aQt[kb][j] - Quad<E>::get(qq, j) * yq);
+            ok[j] = rk * (aKt[kb][j] - Quad<E>::get(kq, j) * yk);
+          }
+          *(QR*)(dqo + kc) = Quad<E>::pack(oq);
+          *(QR*)(dko + kc) = Quad<E>::pack(ok);
+        }
       }
     }
     s1 += lane_xor(s1, 16, lb);
@@ -1001,7 +1052,10 @@ static hipError_t launch_bwd_t(const Params& p, hipStream_t st) {
     q.lead = total >= 8 * cus ? cus / 8 * 8 : 0;   // two workgroups per CU: half of the slots (a multiple of 8)
     q.lead_cycles = 20000;
     prof_mark(ST_INTRA, 0, st);
-    hipLaunchKernelGGL((k_bwd_intra<E, DK, DV>), dim3(total + q.lead), dim3(INTRA_THREADS), 0, st, q);
+    if (p.rnq)
+      hipLaunchKernelGGL((k_bwd_intra<E, DK, DV, true>), dim3(total + q.lead), dim3(INTRA_THREADS), 0, st, q);
+    else
+      hipLaunchKernelGGL((k_bwd_intra<E, DK, DV, false>), dim3(total + q.lead), dim3(INTRA_THREADS), 0, st, q);
     prof_mark(ST_INTRA, 1, st);
   }
   if (p.dlam_sum) {

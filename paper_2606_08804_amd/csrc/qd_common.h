@@ -407,6 +407,7 @@ struct Params {
   const void* q;
   const void* k;
   const void* v;
+  int ldv;               // elements from one (token, head) row of v to the next (Dv, or a wider fused row)
   const float* beta;
   const float* lam;      // per token and head, or nullptr: lambda == lam_c everywhere
   float lam_c;
@@ -431,6 +432,9 @@ struct Params {
   void* dq;
   void* dk;
   void* dv;
+  int ldqk, lddv;        // elements from one (token, head) row to the next in dq and dk, and in dv
+  const float* rnq;      // 1 / |row| of the rows that q and k were normalised from: dq and dk are then the
+  const float* rnk;      // gradients of those rows (negative: clamped row, scaled only); or nullptr
   float* dbeta;
   float* dlam;           // per token and head (lam given), else nullptr
   float* dlam_sum;       // one float: gradient of the constant lambda (lam == nullptr), or nullptr

@@ -561,11 +561,11 @@ __global__ __launch_bounds__(NCW * 64 + 256) void k_scan_fwd(Params p) {
     size_t gi, arow;
     int len;
     chunk_at(c, gi, arow, len);
-    const char* Vg = (const char*)((const E*)p.v + arow * DV + v0);
+    const char* Vg = (const char*)((const E*)p.v + arow * p.ldv + v0);
     dma_lbt<E, 4>(sm.ringB + R::BT, (const char*)((const E*)p.wT + gi * LBT_ELEMS), prod, lane);
     if (!map_tile)
-      dma_rows<R::RO, C, 4, true>(sm.ringB + R::BV_, Vg, (size_t)H * DV * ES, len,
-                                  Vg + (size_t)(len - 1) * H * DV * ES, 0, prod, lane);
+      dma_rows<R::RO, C, 4, true>(sm.ringB + R::BV_, Vg, (size_t)H * p.ldv * ES, len,
+                                  Vg + (size_t)(len - 1) * H * p.ldv * ES, 0, prod, lane);
   };
 
   // state: acc[i][j] = S^T rows 16 (kb0 + i).., columns 16 (ns0 + j).. of this tile

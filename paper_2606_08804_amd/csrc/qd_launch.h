@@ -95,4 +95,8 @@ hipError_t launch_l2norm(int bwd, long rows, int D, long ldx, int dtype, const v
                          const void* y, const float* rn_in, float* rn_out, const void* dy, void* out,
                          hipStream_t st);
 
+// Row L2 normalisation of two tensors of the same strided shape in one launch.
+hipError_t launch_l2norm2(long rows, int D, long ldx, int dtype, const void* x, void* y, float* rn, const void* x2,
+                          void* y2, float* rn2, hipStream_t st);
+
 }  // namespace qd

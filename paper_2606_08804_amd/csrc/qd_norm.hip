@@ -50,7 +50,14 @@ constexpr float NORM_EPS = 1e-12f;
 
 template <typename E, int D>
 __global__ __launch_bounds__(NTHREADS) void k_l2norm_fwd(long rows, long ldx, const E* __restrict__ x,
-                                                        E* __restrict__ y, float* __restrict__ rn) {
+                                                        E* __restrict__ y, float* __restrict__ rn,
+                                                        const E* __restrict__ x2, E* __restrict__ y2,
+                                                        float* __restrict__ rn2) {
+  if (blockIdx.y) {                         // the second of two tensors
+    x = x2;
+    y = y2;
+    rn = rn2;
+  }
   constexpr int L = D * (int)sizeof(E) / 16;
   constexpr int RPB = NTHREADS / L;
   const long row = (long)blockIdx.x * RPB + threadIdx.x / L;
@@ -108,7 +115,7 @@ hipError_t launch_l2norm(int bwd, long rows, int D, long ldx, int dtype, const v
                          (const ET*)y, rn_in, (const ET*)dy, (ET*)out);                        \
     else                                                                                       \
       hipLaunchKernelGGL((k_l2norm_fwd<ET, DV>), grid, dim3(NTHREADS), 0, st, rows, ldx,       \
-                         (const ET*)x, (ET*)out, rn_out);                                      \
+                         (const ET*)x, (ET*)out, rn_out, (const ET*)nullptr, (ET*)nullptr, nullptr);                                      \
   } while (0)
   if (dtype == 1 && D == 128) QD_NORM(__bf16, 128);
   else if (dtype == 1 && D == 64) QD_NORM(__bf16, 64);
@@ -116,6 +123,22 @@ hipError_t launch_l2norm(int bwd, long rows, int D, long ldx, int dtype, const v
   else if (dtype == 0 && D == 64) QD_NORM(float, 64);
   else return hipErrorInvalidValue;
 #undef QD_NORM
+  return hipGetLastError();
+}
+
+hipError_t launch_l2norm2(long rows, int D, long ldx, int dtype, const void* x, void* y, float* rn, const void* x2,
+                          void* y2, float* rn2, hipStream_t st) {
+  if (rows == 0) return hipSuccess;
+#define QD_NORM2(ET, DV)                                                                        \
+  hipLaunchKernelGGL((k_l2norm_fwd<ET, DV>),                                                    \
+                     dim3((unsigned)((rows + NTHREADS / (DV * (int)sizeof(ET) / 16) - 1) /      \
+                                     (NTHREADS / (DV * (int)sizeof(ET) / 16))), 2),             \
+                     dim3(NTHREADS), 0, st, rows, ldx, (const ET*)x, (ET*)y, rn, (const ET*)x2, (ET*)y2, rn2)
+  if (dtype == 1 && D == 128) QD_NORM2(__bf16, 128);
+  else if (dtype == 1 && D == 64) QD_NORM2(__bf16, 64);
+  else if (dtype == 0 && D == 64) QD_NORM2(float, 64);
+  else return hipErrorInvalidValue;
+#undef QD_NORM2
   return hipGetLastError();
 }
 

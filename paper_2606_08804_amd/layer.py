@@ -78,6 +78,37 @@ class L2NormFunction(torch.autograd.Function):
         return _binding.l2norm_bwd(y, rn, dy.contiguous())
 
 
+class QKVChunkFunction(torch.autograd.Function):
+    """L2 normalisation of q and k and the chunkwise recurrence on the rows of
+    the fused projection (qkv [B, T, H, 2 dk + dv]): v is read in place, and the
+    backward writes one gradient of the projection's shape, with the
+    normalisation's backward applied where dq and dk are formed."""
+
+    @staticmethod
+    def forward(ctx, qkv, beta, lam, log_alpha, initial_state, cu_seqlens, dk, dv):
+        ctx.set_materialize_grads(False)         # an unused final state sends no gradient of zeros
+        need = any(ctx.needs_input_grad[:5])
+        o, final_state, normed, saved = _binding.layer_fwd(qkv, beta, lam, log_alpha, initial_state, cu_seqlens,
+                                                           dk, dv, need)
+        ctx.dims = dk, dv
+        ctx.lam_const = None if isinstance(lam, torch.Tensor) else lam
+        lam_t = lam if isinstance(lam, torch.Tensor) else None
+        ctx.save_for_backward(qkv, beta, lam_t, log_alpha, initial_state, cu_seqlens, saved, *normed)
+        return o, final_state
+
+    @staticmethod
+    def backward(ctx, d_o, d_final_state):
+        qkv, beta, lam_t, log_alpha, initial_state, cu_seqlens, saved, *normed = ctx.saved_tensors
+        need_dS0 = initial_state is not None and ctx.needs_input_grad[4]
+        if d_o is None:
+            d_o = torch.zeros(qkv.shape[:-1] + (ctx.dims[1],), dtype=qkv.dtype, device=qkv.device)
+        dSf = None if d_final_state is None else d_final_state.contiguous()
+        dqkv, dbeta, dlam, dla, dS0 = _binding.layer_bwd(
+            qkv, normed, beta, lam_t if lam_t is not None else ctx.lam_const, log_alpha, initial_state, cu_seqlens,
+            *ctx.dims, saved, d_o.contiguous(), dSf, need_dS0)
+        return dqkv, dbeta, dlam, dla, dS0, None, None, None
+
+
 def qdelta_chunk(q, k, v, beta, lam=None, log_alpha=None, initial_state=None, cu_seqlens=None):
     """Differentiable chunkwise Q-Delta.  Layouts as the C ABI: q, k [B,T,H,Dk],
     v [B,T,H,Dv] (bf16 or fp32), gates [B,T,H] fp32, states [N,H,Dv,Dk] fp32."""
@@ -131,18 +162,30 @@ class QDeltaLayer(torch.nn.Module):
         log_alpha = F.logsigmoid(g[..., nxt:]) if self.use_decay else None
         return beta, lam, log_alpha
 
+    def _fused_rows(self, qkv):
+        """Whether the kernels read the projection's rows in place: the head
+        sizes and types that the chunk kernels take, whole aligned rows.
+        Everything else goes through the separate q, k and v tensors."""
+        return (qkv.is_cuda and qkv.numel() > 0 and qkv.is_contiguous() and qkv.data_ptr() % 16 == 0
+                and self.dv in (64, 128, 256)
+                and (qkv.dtype == torch.bfloat16 and self.dk in (64, 128)
+                     or qkv.dtype == torch.float32 and self.dk == 64))
+
     def forward(self, h, initial_state=None, cu_seqlens=None, output_final_state=False):
         B, T, _ = h.shape
         H, dk, dv = self.H, self.dk, self.dv
         qkv = self.w_qkv(h).view(B, T, H, 2 * dk + dv)
-        q, k, v = qkv.split([dk, dk, dv], dim=-1)
-        if self.qk_norm:
-            q = L2NormFunction.apply(q)
-            k = L2NormFunction.apply(k)
         beta, lam, log_alpha = self.gates(h)
-        o, final_state = qdelta_chunk(q.contiguous(), k.contiguous(), v.contiguous(),
-                                      beta.contiguous(), lam.contiguous() if isinstance(lam, torch.Tensor) else lam,
-                                      None if log_alpha is None else log_alpha.contiguous(),
-                                      initial_state, cu_seqlens)
+        gates = (beta.contiguous(), lam.contiguous() if isinstance(lam, torch.Tensor) else lam,
+                 None if log_alpha is None else log_alpha.contiguous())
+        if self.qk_norm and self._fused_rows(qkv):
+            o, final_state = QKVChunkFunction.apply(qkv, *gates, initial_state, cu_seqlens, dk, dv)
+        else:
+            q, k, v = qkv.split([dk, dk, dv], dim=-1)
+            if self.qk_norm:
+                q = L2NormFunction.apply(q)
+                k = L2NormFunction.apply(k)
+            o, final_state = qdelta_chunk(q.contiguous(), k.contiguous(), v.contiguous(), *gates, initial_state,
+                                          cu_seqlens)
         y = self.w_out(o.reshape(B, T, H * dv))
         return (y, final_state) if output_final_state else y

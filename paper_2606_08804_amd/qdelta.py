@@ -116,6 +116,12 @@ def lib():
         L.qdelta_l2norm_fwd.restype = ctypes.c_int
         L.qdelta_l2norm_bwd.argtypes = [i64, i32, i32, P, P, P, P, P]
         L.qdelta_l2norm_bwd.restype = ctypes.c_int
+        # B, T, N, cu, H, Dk, Dv, dtype, qkv, gates, S0, q, k, rnorms, o, Sf, saved, ws, bytes, stream
+        L.qdelta_layer_fwd.argtypes = [i32] * 3 + [P] + [i32] * 4 + [P] * 3 + [f32] + [P] * 10 + [sz, P]
+        L.qdelta_layer_fwd.restype = ctypes.c_int
+        # ..., qkv, q, k, rnorms, gates, S0, saved, dO, dSf, dqkv, dbeta, dlam, dla, dS0, ws, bytes, stream
+        L.qdelta_layer_bwd.argtypes = [i32] * 3 + [P] + [i32] * 4 + [P] * 7 + [f32] + [P] * 11 + [sz, P]
+        L.qdelta_layer_bwd.restype = ctypes.c_int
         L.qdelta_profile_begin.argtypes = []
         L.qdelta_profile_begin.restype = ctypes.c_int
         L.qdelta_profile_end.argtypes = [P, P]
@@ -499,6 +505,73 @@ def l2norm_bwd(y, rn, dy):
     _check("qdelta_l2norm_bwd", lib().qdelta_l2norm_bwd(y.numel() // y.shape[-1], y.shape[-1], _dt(y),
                                                         _p(y), _p(rn), _p(dy), _p(dx), _stream()))
     return dx
+
+
+def layer_fwd(qkv, beta, lam, log_alpha, initial_state, cu_seqlens, Dk, Dv, save_states):
+    """The layer's recurrence on the rows of its fused projection (qkv
+    [B, T, H, 2 Dk + Dv], q | k | v per row): q and k normalised per row, v read
+    in place.  Returns (o, final_state, (q, k, rnorm_q, rnorm_k), saved)."""
+    L = lib()
+    dt = _dt(qkv)
+    B, T, H, _ = qkv.shape
+    act = qkv.shape[:-1]
+    N = B if cu_seqlens is None else cu_seqlens.numel() - 1
+    _need(qkv, "qkv", qkv.dtype, tuple(act) + (2 * Dk + Dv,))
+    if cu_seqlens is not None:
+        if B != 1:
+            raise ValueError("a packed batch has leading dimension 1")
+        _need(cu_seqlens, "cu_seqlens", torch.int32)
+    _need(beta, "beta", torch.float32, act)
+    lam_t, lam_c = _lam(lam, act)
+    _opt(log_alpha, "log_alpha", torch.float32, act)
+    _opt(initial_state, "initial_state", torch.float32, (N, H, Dv, Dk))
+    dev = qkv.device
+    q = torch.empty(tuple(act) + (Dk,), dtype=qkv.dtype, device=dev)
+    k = torch.empty_like(q)
+    rq = torch.empty(act, dtype=torch.float32, device=dev)
+    rk = torch.empty_like(rq)
+    o = torch.empty(tuple(act) + (Dv,), dtype=qkv.dtype, device=dev)
+    Sf = torch.empty((N, H, Dv, Dk), dtype=torch.float32, device=dev)
+    n_seqs = N if cu_seqlens is not None else 0
+    saved = None
+    if save_states:
+        saved = torch.empty(saved_bytes(B, T, H, Dk, Dv, dt, n_seqs), dtype=torch.uint8, device=dev)
+    nbytes = workspace_bytes(B, T, H, Dk, Dv, dt, n_seqs, False)
+    ws = _workspace(nbytes, dev, None)
+    _check("qdelta_layer_fwd",
+           L.qdelta_layer_fwd(B, T, N, _p(cu_seqlens), H, Dk, Dv, dt, _p(qkv), _p(beta), _p(lam_t), lam_c,
+                              _p(log_alpha), _p(initial_state), _p(q), _p(k), _p(rq), _p(rk), _p(o), _p(Sf),
+                              _p(saved), _p(ws), nbytes, _stream()))
+    return o, Sf, (q, k, rq, rk), saved
+
+
+def layer_bwd(qkv, normed, beta, lam, log_alpha, initial_state, cu_seqlens, Dk, Dv, saved, d_o, d_final_state,
+              need_d_initial_state):
+    """Gradients of layer_fwd: (dqkv, dbeta, dlam, dlog_alpha, d_initial_state); dlam None without a lambda tensor."""
+    L = lib()
+    dt = _dt(qkv)
+    B, T, H, _ = qkv.shape
+    act = qkv.shape[:-1]
+    N = B if cu_seqlens is None else cu_seqlens.numel() - 1
+    q, k, rq, rk = normed
+    _need(qkv, "qkv", qkv.dtype, tuple(act) + (2 * Dk + Dv,))
+    lam_t, lam_c = _lam(lam, act)
+    _need(d_o, "d_o", qkv.dtype, tuple(act) + (Dv,))
+    _opt(d_final_state, "d_final_state", torch.float32, (N, H, Dv, Dk))
+    dev = qkv.device
+    dqkv = torch.empty_like(qkv)
+    dbeta = torch.empty_like(beta)
+    dlam = torch.empty_like(lam_t) if lam_t is not None else None
+    dla = torch.empty_like(log_alpha) if log_alpha is not None else None
+    dS0 = torch.empty((N, H, Dv, Dk), dtype=torch.float32, device=dev) if need_d_initial_state else None
+    nbytes = workspace_bytes(B, T, H, Dk, Dv, dt, N if cu_seqlens is not None else 0, True)
+    ws = _workspace(nbytes, dev, None)
+    _check("qdelta_layer_bwd",
+           L.qdelta_layer_bwd(B, T, N, _p(cu_seqlens), H, Dk, Dv, dt, _p(qkv), _p(q), _p(k), _p(rq), _p(rk), _p(beta),
+                              _p(lam_t), lam_c, _p(log_alpha), _p(initial_state), _p(saved), _p(d_o),
+                              _p(d_final_state), _p(dqkv), _p(dbeta), _p(dlam), _p(dla), _p(dS0), _p(ws), nbytes,
+                              _stream()))
+    return dqkv, dbeta, dlam, dla, dS0
 
 
 def profile_begin():

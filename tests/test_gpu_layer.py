@@ -99,3 +99,44 @@ def test_l2norm_kernels_match_normalize(dt, D):
     assert normwise(y.double().cpu().numpy(), yr.detach().numpy()) <= tol
     assert normwise(dx.double().cpu().numpy(), xr.grad.numpy()) <= tol
     assert float(rn[3, 4, 5]) < 0 and torch.all(y[3, 4, 5] == 0)
+
+
+@pytest.mark.parametrize("dt,dk,dv,lengths", [(torch.bfloat16, 128, 128, None), (torch.bfloat16, 64, 256, None),
+                                              (torch.bfloat16, 128, 64, [70, 0, 1, 199]), (torch.float32, 64, 128, None),
+                                              (torch.float32, 64, 64, [64, 206])])
+def test_fused_rows_equal_separate_tensors(dt, dk, dv, lengths):
+    """The recurrence on the projection's rows in place against the same rows split into q, k and v tensors: equal
+    outputs, the gradient of the rows within the rounding of dq and dk that the separate form stores (2^-9 in bf16;
+    one row of q and one of k zero, so clamped), equal gate and state gradients."""
+    g = torch.Generator().manual_seed(47)
+    B, T, H = (1, 270, 3) if lengths else (2, 135, 3)
+    N = len(lengths) if lengths else B
+    cu = torch.tensor([0] + lengths, dtype=torch.int32).cumsum(0).to(torch.int32).cuda() if lengths else None
+    qkv = torch.randn(B, T, H, 2 * dk + dv, generator=g)
+    qkv[0, 5, 1, :dk] = 0.0
+    qkv[0, 9, 2, dk:2 * dk] = 0.0
+    qkv = qkv.to(dt).cuda()
+    gates = [torch.sigmoid(torch.randn(B, T, H, generator=g)).cuda(), torch.sigmoid(torch.randn(B, T, H, generator=g)).cuda(),
+             torch.nn.functional.logsigmoid(torch.randn(B, T, H, generator=g)).cuda()]
+    S0 = (0.1 * torch.randn(N, H, dv, dk, generator=g)).cuda()
+    do = torch.randn(B, T, H, dv, generator=g).to(dt).cuda()
+    dS = torch.randn(N, H, dv, dk, generator=g).cuda()
+
+    def grads(f):
+        xs = [t.clone().requires_grad_() for t in (qkv, *gates, S0)]
+        o, Sf = f(*xs)
+        return (o, Sf) + torch.autograd.grad((o, Sf), xs, (do, dS))
+
+    def separate(x, b, lam, la, s):
+        q, k, v = x.split([dk, dk, dv], dim=-1)
+        return layer.qdelta_chunk(layer.L2NormFunction.apply(q), layer.L2NormFunction.apply(k), v.contiguous(), b, lam,
+                                  la, s, cu)
+
+    fused = grads(lambda x, b, lam, la, s: layer.QKVChunkFunction.apply(x, b, lam, la, s, cu, dk, dv))
+    apart = grads(separate)
+    torch.cuda.synchronize()
+    for i in (0, 1, 3, 4, 5, 6):
+        assert torch.equal(fused[i], apart[i]), i
+    tol = 2.0 ** -8 if dt == torch.bfloat16 else 1e-6
+    assert normwise(fused[2].double().cpu().numpy(), apart[2].double().cpu().numpy()) <= tol
+    assert torch.equal(fused[2][..., 2 * dk:], apart[2][..., 2 * dk:])
