@@ -1,6 +1,6 @@
 /* Entry points of libqdelta.so that only the autograd layer
  * (paper_2606_08804_amd/layer.py) calls: the chunk forward and backward on
- * the rows of its fused projection.  They return the status codes of qdelta.h
+ * the rows of its fused projection, and its gates.  They return the status codes of qdelta.h
  * and follow its conventions (device pointers, 16-byte alignment,
  * asynchronous on the caller's stream). */
 #ifndef QDELTA_LAYER_H
@@ -32,6 +32,21 @@ int qdelta_layer_bwd(int32_t B, int32_t T, int32_t N, const int32_t* cu_seqlens,
                      const float* log_alpha, const float* initial_state, const void* saved, const void* d_o,
                      const float* d_final_state, void* dqkv, float* dbeta, float* dlam, float* dlog_alpha,
                      float* d_initial_state, void* ws, size_t ws_bytes, hipStream_t stream);
+
+/* Gates from logits [tokens, n H] (dtype; contiguous rows of beta, then lambda
+ * and alpha where lam and log_alpha are not NULL): beta = sigmoid(x),
+ * lam = sigmoid(x + *bias) (one value of bias_dtype), log_alpha =
+ * logsigmoid(x), each [tokens, H] fp32. */
+int qdelta_layer_gates_fwd(int64_t tokens, int32_t H, int32_t dtype, int32_t bias_dtype, const void* logits,
+                           const void* bias, float* beta, float* lam, float* log_alpha, hipStream_t stream);
+
+/* Backward, from the gates themselves: dlogits like logits, *dbias the bias's
+ * gradient (when lam is not NULL; parts: qdelta_layer_gate_parts floats of
+ * workspace).  A NULL dbeta, dlam or dlog_alpha is a gradient of zeros. */
+int32_t qdelta_layer_gate_parts(int64_t tokens, int32_t H);
+int qdelta_layer_gates_bwd(int64_t tokens, int32_t H, int32_t dtype, int32_t bias_dtype, const float* beta,
+                           const float* lam, const float* log_alpha, const float* dbeta, const float* dlam,
+                           const float* dlog_alpha, void* dlogits, float* parts, void* dbias, hipStream_t stream);
 
 #ifdef __cplusplus
 }

@@ -763,6 +763,33 @@ int qdelta_layer_bwd(int32_t B, int32_t T, int32_t N, const int32_t* cu_seqlens,
                   rnorm_q, rnorm_k);
 }
 
+static bool gate_args(int64_t tokens, int32_t H, int32_t dtype, int32_t bias_dtype) {
+  return tokens > 0 && H > 0 && tokens * H < (int64_t(1) << 31) && (dtype == QDELTA_F32 || dtype == QDELTA_BF16) &&
+         (bias_dtype == QDELTA_F32 || bias_dtype == QDELTA_BF16);
+}
+
+int32_t qdelta_layer_gate_parts(int64_t tokens, int32_t H) {
+  return tokens > 0 && H > 0 ? qd::gates_blocks((long)(tokens * H)) : 0;
+}
+
+int qdelta_layer_gates_fwd(int64_t tokens, int32_t H, int32_t dtype, int32_t bias_dtype, const void* logits,
+                           const void* bias, float* beta, float* lam, float* log_alpha, hipStream_t stream) {
+  if (!gate_args(tokens, H, dtype, bias_dtype) || !logits || !beta || (lam && !bias)) return QDELTA_EINVAL;
+  const int ld = H * (1 + (lam != nullptr) + (log_alpha != nullptr));
+  return qd::launch_gates_fwd((long)(tokens * H), H, ld, dtype, bias_dtype, logits, bias, beta, lam, log_alpha,
+                              stream) == hipSuccess ? QDELTA_OK : QDELTA_EHIP;
+}
+
+int qdelta_layer_gates_bwd(int64_t tokens, int32_t H, int32_t dtype, int32_t bias_dtype, const float* beta,
+                           const float* lam, const float* log_alpha, const float* dbeta, const float* dlam,
+                           const float* dlog_alpha, void* dlogits, float* parts, void* dbias, hipStream_t stream) {
+  if (!gate_args(tokens, H, dtype, bias_dtype) || !beta || !dlogits || (lam && (!parts || !dbias)))
+    return QDELTA_EINVAL;
+  const int ld = H * (1 + (lam != nullptr) + (log_alpha != nullptr));
+  return qd::launch_gates_bwd((long)(tokens * H), H, ld, dtype, bias_dtype, beta, lam, log_alpha, dbeta, dlam,
+                              dlog_alpha, dlogits, parts, dbias, stream) == hipSuccess ? QDELTA_OK : QDELTA_EHIP;
+}
+
 int qdelta_recurrent_step(int32_t N, int32_t H, int32_t Dk, int32_t Dv, int32_t dtype,
                           const void* q, const void* k, const void* v, const float* beta,
                           const float* lam, float lam_scalar, const float* log_alpha, float* state,

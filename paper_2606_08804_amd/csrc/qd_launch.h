@@ -99,4 +99,13 @@ hipError_t launch_l2norm(int bwd, long rows, int D, long ldx, int dtype, const v
 hipError_t launch_l2norm2(long rows, int D, long ldx, int dtype, const void* x, void* y, float* rn, const void* x2,
                           void* y2, float* rn2, hipStream_t st);
 
+// Layer gates from rows of logits (ld apart) over n (token, head) pairs, and
+// their backward; lam / la nullptr where not learned.  part holds gates_blocks(n) floats.
+int gates_blocks(long n);
+hipError_t launch_gates_fwd(long n, int H, int ld, int dtype, int bias_dtype, const void* x, const void* bias,
+                            float* beta, float* lam, float* la, hipStream_t st);
+hipError_t launch_gates_bwd(long n, int H, int ld, int dtype, int bias_dtype, const float* beta, const float* lam,
+                            const float* la, const float* dbeta, const float* dlam, const float* dla, void* dx,
+                            float* part, void* dbias, hipStream_t st);
+
 }  // namespace qd

@@ -78,6 +78,24 @@ class L2NormFunction(torch.autograd.Function):
         return _binding.l2norm_bwd(y, rn, dy.contiguous())
 
 
+class GatesFunction(torch.autograd.Function):
+    """QDeltaLayer.gates from the gate projection's rows (bias: the lambda
+    bias, None for a fixed lambda), one launch forward and two backward."""
+
+    @staticmethod
+    def forward(ctx, logits, bias, H, has_decay):
+        ctx.set_materialize_grads(False)
+        beta, lam, la = _binding.layer_gates_fwd(logits, bias, H, has_decay)
+        ctx.types = logits.dtype, None if bias is None else bias.dtype
+        ctx.save_for_backward(beta, lam, la)
+        return beta, lam, la
+
+    @staticmethod
+    def backward(ctx, dbeta, dlam, dla):
+        dx, dbias = _binding.layer_gates_bwd(*ctx.saved_tensors, dbeta, dlam, dla, *ctx.types)
+        return dx, dbias, None, None
+
+
 class QKVChunkFunction(torch.autograd.Function):
     """L2 normalisation of q and k and the chunkwise recurrence on the rows of
     the fused projection (qkv [B, T, H, 2 dk + dv]): v is read in place, and the
@@ -149,8 +167,11 @@ class QDeltaLayer(torch.nn.Module):
     def gates(self, h):
         """beta, lambda, log alpha ([..., H] fp32 or wider; lambda a number
         when fixed, log alpha None without decay)."""
-        acc = torch.promote_types(h.dtype, torch.float32)
-        g = self.w_gates(h).to(acc)
+        return self._split_gates(self.w_gates(h), h.dtype)
+
+    def _split_gates(self, g, dtype):
+        acc = torch.promote_types(dtype, torch.float32)
+        g = g.to(acc)
         H = self.H
         beta = torch.sigmoid(g[..., :H])
         nxt = H
@@ -161,6 +182,23 @@ class QDeltaLayer(torch.nn.Module):
             lam = self.fixed_lambda
         log_alpha = F.logsigmoid(g[..., nxt:]) if self.use_decay else None
         return beta, lam, log_alpha
+
+    def _can_fuse_gates(self, h):
+        """Whether gates() may be replaced by its kernels: on the GPU, in the
+        types they take, with gates() and the scalar bias as defined here."""
+        bias = getattr(self, "lambda_bias", None)
+        return (h.is_cuda and h.numel() > 0 and h.dtype in (torch.bfloat16, torch.float32)
+                and type(self).gates is QDeltaLayer.gates and "gates" not in self.__dict__
+                and (bias is None or bias.is_cuda and bias.dim() == 0 and bias.dtype in (torch.bfloat16, torch.float32)))
+
+    def _fused_gates(self, h):
+        logits = self.w_gates(h)
+        n_gates = 1 + (self.fixed_lambda is None) + bool(self.use_decay)
+        if logits.dtype not in (torch.bfloat16, torch.float32) or logits.shape[-1] != n_gates * self.H:
+            return self._split_gates(logits, h.dtype)
+        bias = self.lambda_bias if self.fixed_lambda is None else None
+        beta, lam, log_alpha = GatesFunction.apply(logits.contiguous(), bias, self.H, bool(self.use_decay))
+        return beta, lam if self.fixed_lambda is None else self.fixed_lambda, log_alpha
 
     def _fused_rows(self, qkv):
         """Whether the kernels read the projection's rows in place: the head
@@ -175,7 +213,7 @@ class QDeltaLayer(torch.nn.Module):
         B, T, _ = h.shape
         H, dk, dv = self.H, self.dk, self.dv
         qkv = self.w_qkv(h).view(B, T, H, 2 * dk + dv)
-        beta, lam, log_alpha = self.gates(h)
+        beta, lam, log_alpha = self._fused_gates(h) if self._can_fuse_gates(h) else self.gates(h)
         gates = (beta.contiguous(), lam.contiguous() if isinstance(lam, torch.Tensor) else lam,
                  None if log_alpha is None else log_alpha.contiguous())
         if self.qk_norm and self._fused_rows(qkv):

@@ -122,6 +122,12 @@ def lib():
         # ..., qkv, q, k, rnorms, gates, S0, saved, dO, dSf, dqkv, dbeta, dlam, dla, dS0, ws, bytes, stream
         L.qdelta_layer_bwd.argtypes = [i32] * 3 + [P] + [i32] * 4 + [P] * 7 + [f32] + [P] * 11 + [sz, P]
         L.qdelta_layer_bwd.restype = ctypes.c_int
+        L.qdelta_layer_gate_parts.argtypes = [i64, i32]
+        L.qdelta_layer_gate_parts.restype = i32
+        L.qdelta_layer_gates_fwd.argtypes = [i64, i32, i32, i32] + [P] * 6
+        L.qdelta_layer_gates_fwd.restype = ctypes.c_int
+        L.qdelta_layer_gates_bwd.argtypes = [i64, i32, i32, i32] + [P] * 10
+        L.qdelta_layer_gates_bwd.restype = ctypes.c_int
         L.qdelta_profile_begin.argtypes = []
         L.qdelta_profile_begin.restype = ctypes.c_int
         L.qdelta_profile_end.argtypes = [P, P]
@@ -572,6 +578,39 @@ def layer_bwd(qkv, normed, beta, lam, log_alpha, initial_state, cu_seqlens, Dk, 
                               _p(d_final_state), _p(dqkv), _p(dbeta), _p(dlam), _p(dla), _p(dS0), _p(ws), nbytes,
                               _stream()))
     return dqkv, dbeta, dlam, dla, dS0
+
+
+def layer_gates_fwd(logits, bias, H, has_decay):
+    """Gates of the layer from its gate projection's rows (beta | lambda | alpha
+    logits; lambda when bias is given, alpha with decay), each [..., H] fp32 (None where not learned)."""
+    _need(logits, "logits")
+    act = tuple(logits.shape[:-1]) + (H,)
+    tokens = logits.numel() // logits.shape[-1]
+    beta = torch.empty(act, dtype=torch.float32, device=logits.device)
+    lam = torch.empty_like(beta) if bias is not None else None
+    la = torch.empty_like(beta) if has_decay else None
+    _check("qdelta_layer_gates_fwd", lib().qdelta_layer_gates_fwd(
+        tokens, H, _dt(logits), _dt(bias) if bias is not None else QDELTA_F32, _p(logits), _p(bias), _p(beta), _p(lam),
+        _p(la), _stream()))
+    return beta, lam, la
+
+
+def layer_gates_bwd(beta, lam, la, dbeta, dlam, dla, dtype, bias_dtype):
+    """Gradients of layer_gates_fwd: (dlogits in dtype, dbias or None)."""
+    H = beta.shape[-1]
+    tokens = beta.numel() // H
+    n = 1 + (lam is not None) + (la is not None)
+    dx = torch.empty(tuple(beta.shape[:-1]) + (n * H,), dtype=dtype, device=beta.device)
+    parts = dbias = None
+    if lam is not None:
+        parts = torch.empty(lib().qdelta_layer_gate_parts(tokens, H), dtype=torch.float32, device=beta.device)
+        dbias = torch.empty((), dtype=bias_dtype, device=beta.device)
+    grads = [None if d is None else _need(d.contiguous(), "gate gradient", torch.float32, tuple(beta.shape))
+             for d in (dbeta, dlam, dla)]
+    _check("qdelta_layer_gates_bwd", lib().qdelta_layer_gates_bwd(
+        tokens, H, _dt(dx), _dt(dbias) if dbias is not None else QDELTA_F32, _p(beta), _p(lam), _p(la),
+        *[_p(d) for d in grads], _p(dx), _p(parts), _p(dbias), _stream()))
+    return dx, dbias
 
 
 def profile_begin():

@@ -140,3 +140,41 @@ def test_fused_rows_equal_separate_tensors(dt, dk, dv, lengths):
     tol = 2.0 ** -8 if dt == torch.bfloat16 else 1e-6
     assert normwise(fused[2].double().cpu().numpy(), apart[2].double().cpu().numpy()) <= tol
     assert torch.equal(fused[2][..., 2 * dk:], apart[2][..., 2 * dk:])
+
+
+@pytest.mark.parametrize("dt,use_decay,fixed_lambda", [(torch.bfloat16, True, None), (torch.float32, False, None),
+                                                       (torch.float32, True, 0.5), (torch.bfloat16, False, 0.0)])
+@pytest.mark.parametrize("B,T,H", [(1, 1, 1), (2, 65, 3), (3, 1001, 16)])
+def test_gate_kernels_match_gates(dt, use_decay, fixed_lambda, B, T, H):
+    """The gate kernels against gates() itself in fp64 on the same logits (a saturated one of each sign among them):
+    values and logit gradients to the rounding of fp32 (bf16 gradients: 2^-8), the bias's gradient relative to the
+    sum of its summands' magnitudes."""
+    m = layer.QDeltaLayer(d_model=8, n_heads=H, head_dk=64, head_dv=64, use_decay=use_decay, fixed_lambda=fixed_lambda)
+    g = torch.Generator().manual_seed(48)
+    n = m.w_gates.out_features
+    x = torch.randn(B, T, n, generator=g)
+    x[0, 0, 0], x[-1, -1, -1] = 40.0, -40.0
+    x = x.to(dt)
+    bias = torch.tensor(-0.8, dtype=dt) if fixed_lambda is None else None
+    dy = [torch.randn(B, T, H, generator=g) for _ in range(3)]
+
+    xr = x.double().requires_grad_()
+    br = None if bias is None else bias.double().expand(B, T, H).clone().requires_grad_()
+    if br is not None:
+        m.lambda_bias = torch.nn.Parameter(br.detach().clone())
+    ref = m._split_gates(xr, torch.float64)
+    xg = x.cuda().requires_grad_()
+    bg = None if bias is None else bias.cuda().requires_grad_()
+    got = layer.GatesFunction.apply(xg, bg, H, use_decay)
+    live = [(a, b, d) for a, b, d in zip(got, ref, dy) if a is not None]
+    torch.autograd.backward([a for a, _, _ in live], [d.cuda() for _, _, d in live])
+    torch.autograd.backward([b for _, b, _ in live], [d.double() for _, _, d in live])
+    torch.cuda.synchronize()
+    for a, b, _ in live:
+        assert torch.allclose(a.cpu().double(), b.detach(), rtol=1e-6, atol=1e-30)
+    tol = dict(rtol=2.0 ** -8, atol=1e-30) if dt == torch.bfloat16 else dict(rtol=2e-6, atol=1e-7)
+    assert torch.allclose(xg.grad.cpu().double(), xr.grad, **tol)
+    if bias is not None:
+        terms = m.lambda_bias.grad
+        err = abs(float(bg.grad) - float(terms.sum())) / float(terms.abs().sum())
+        assert err <= (2.0 ** -8 if dt == torch.bfloat16 else 1e-6)
