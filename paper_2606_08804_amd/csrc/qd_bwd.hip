@@ -501,7 +501,8 @@ __global__ __launch_bounds__(INTRA_THREADS) __attribute__((amdgpu_waves_per_eu(i
   const char* dSg = (const char*)((const E*)p.w_dSo + gi * DK * DV);
   const char* Dg = (const char*)((const E*)p.savedD + gi * C * DV);   // 32-column tiles, C x 32 each
   const char* dOg = (const char*)((const E*)p.dO + arow * DV);
-  const char* Vg = (const char*)((const E*)p.v + arow * p.ldv);
+  const int ldv = NORM ? p.ldv : DV;        // (the fused rows come with the normalisation)
+  const char* Vg = (const char*)((const E*)p.v + arow * ldv);
   // the gate block (b, beta, lambda; waves 0-2 one vector each, straight
   // into LDS) and this wave's rows of K as B operands of Kbar dS'^T (k = key;
   // rows past the chunk re-read its last row: their dD rows are zeroed),
@@ -523,7 +524,7 @@ __global__ __launch_bounds__(INTRA_THREADS) __attribute__((amdgpu_waves_per_eu(i
     dma_rows<RK, BV, NWAVES, true>(t + TA::S, Sg + vb * RK, RK, BV, Sg, 0, w, ln);
     dma_rows<RK, BV, NWAVES, true>(t + TA::DS, dSg + vb * RK, RK, BV, dSg, 0, w, ln);
     dma_rows<TA::RE, C, NWAVES, true>(t + TA::D, Dt, TA::RE, C, Dt, 0, w, ln);
-    dma_rows<TA::RE, C, NWAVES, true>(t + TA::V, Vg + vb * ES, (size_t)H * p.ldv * ES, len, Dt, TA::RE, w, ln);
+    dma_rows<TA::RE, C, NWAVES, true>(t + TA::V, Vg + vb * ES, (size_t)H * ldv * ES, len, Dt, TA::RE, w, ln);
     dma_rows<TA::RE, C, NWAVES, true>(t + TA::DO, dOg + vb * ES, (size_t)H * DV * ES, len, Dt, TA::RE, w, ln);
   };
   // this wave's rows of the tile's dD, as their transpose (value rows, chunk
@@ -863,8 +864,8 @@ __global__ __launch_bounds__(INTRA_THREADS) __attribute__((amdgpu_waves_per_eu(i
     const float gr = sm.g[rr], lr = sm.lam[rr], kbr = __expf(sm.b[C - 1] - sm.b[rr]);
     float s1 = 0.f, s2 = 0.f, s3 = 0.f;
     const size_t orow = arow + (size_t)rr * H;
-    E* dqo = (E*)p.dq + orow * p.ldqk;
-    E* dko = (E*)p.dk + orow * p.ldqk;
+    E* dqo = (E*)p.dq + orow * (NORM ? p.ldqk : DK);
+    E* dko = (E*)p.dk + orow * (NORM ? p.ldqk : DK);
     // NORM: 1 / |row| of the rows behind q and k, and y . dy of this row
     float rq = 0.f, rk = 0.f, yq = 0.f, yk = 0.f;
     if (NORM && rr < len) {

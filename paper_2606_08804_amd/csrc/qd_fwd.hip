@@ -509,6 +509,7 @@ __global__ __launch_bounds__(NCW * 64 + 256) void k_scan_fwd(Params p) {
   const int unit = G ? su : su / nseg, g = G ? 0 : su % nseg;
   const bool map_tile = SEG == SEG_MAPS && vt >= NVT;  // rows of the segment's A (no values)
   const int H = p.H, n = unit / H, h = unit % H;
+  const size_t vstride = (size_t)H * p.ldv * ES;       // bytes from one token's row of V to the next
   const int v0 = map_tile ? 0 : vt * BV;               // V columns read (a map tile's are ignored)
   const int r0 = vt * BV;                              // first state row (map rows follow the value rows)
   int s, e;
@@ -564,8 +565,8 @@ __global__ __launch_bounds__(NCW * 64 + 256) void k_scan_fwd(Params p) {
     const char* Vg = (const char*)((const E*)p.v + arow * p.ldv + v0);
     dma_lbt<E, 4>(sm.ringB + R::BT, (const char*)((const E*)p.wT + gi * LBT_ELEMS), prod, lane);
     if (!map_tile)
-      dma_rows<R::RO, C, 4, true>(sm.ringB + R::BV_, Vg, (size_t)H * p.ldv * ES, len,
-                                  Vg + (size_t)(len - 1) * H * p.ldv * ES, 0, prod, lane);
+      dma_rows<R::RO, C, 4, true>(sm.ringB + R::BV_, Vg, vstride, len, Vg + (size_t)(len - 1) * vstride, 0, prod,
+                                  lane);
   };
 
   // state: acc[i][j] = S^T rows 16 (kb0 + i).., columns 16 (ns0 + j).. of this tile

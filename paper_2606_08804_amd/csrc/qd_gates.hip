@@ -15,8 +15,6 @@ namespace qd {
 
 namespace {
 
-constexpr int GATE_PER = 4;       // (token, head) pairs per thread
-
 __device__ inline float sigmoid(float x) { return 1.f / (1.f + expf(-x)); }
 
 // Sum over the workgroup in a fixed order, in thread 0.
@@ -88,7 +86,7 @@ __global__ __launch_bounds__(NTHREADS) void k_gates_bias(int n, const float* __r
 
 // workgroups for n (token, head) pairs
 int gates_blocks(long n) {
-  const long b = (n + NTHREADS * GATE_PER - 1) / (NTHREADS * GATE_PER);
+  const long b = (n + NTHREADS - 1) / NTHREADS;
   return (int)(b < 1 ? 1 : b > 1024 ? 1024 : b);
 }
 
