@@ -140,15 +140,24 @@ __global__ __launch_bounds__(NCW * 64 + 256) void k_scan_bwd(Params p) {
     gi = (size_t)(base + c) * H + h;
     arow = (size_t)t0 * H + h;
   };
-  // producers: Q of the chunk of iteration it (rows past the chunk re-read
-  // its last row: they only meet zero dO rows and zero gates)
+  // lane offsets of the producers' loads within a chunk (dma_rows_full)
+  const size_t kstride = (size_t)H * R::RK, ostride = (size_t)H * DV * sizeof(E);
+  const uint32_t koff = dma_off<R::RK, 4>(kstride, prod & 3, lane), ooff = dma_off<R::RO, 4>(ostride, prod & 3, lane);
+  const LbtLane<E, 4> lbt(prod & 3, lane);
+  const bool kfit = rows_fit(C, kstride), ofit = rows_fit(C, ostride);
+  // rows past the chunk re-read its last row: they only meet zero dO rows and
+  // zero gates
+  auto issue_keys = [&](const void* src, size_t arow, int len, char* dst) {
+    const char* g = (const char*)((const E*)src + arow * DK);
+    if (len == C && kfit) dma_rows_full<R::RK, C, 4>(dst, g, kstride, koff, prod);
+    else dma_rows<R::RK, C, 4, true>(dst, g, kstride, len, g + (size_t)(len - 1) * kstride, 0, prod, lane);
+  };
+  // producers: Q of the chunk of iteration it
   auto issueQ = [&](int it) {
     size_t gi, arow;
     int len;
     chunk_at(nch - 1 - it, gi, arow, len);
-    const char* Qg = (const char*)((const E*)p.q + arow * DK);
-    dma_rows<R::RK, C, 4, true>(sm.ringX[it % NA] + R::XQ, Qg, (size_t)H * R::RK, len,
-                                Qg + (size_t)(len - 1) * H * R::RK, 0, prod, lane);
+    issue_keys(p.q, arow, len, sm.ringX[it % NA] + R::XQ);
   };
   // producers: K, dO (rows past the chunk from the preparation's zero block)
   // and the gates
@@ -157,25 +166,24 @@ __global__ __launch_bounds__(NCW * 64 + 256) void k_scan_bwd(Params p) {
     int len;
     chunk_at(nch - 1 - it, gi, arow, len);
     char* r = sm.ringX[it % NA];
-    const char* Kg = (const char*)((const E*)p.k + arow * DK);
     const char* Og = (const char*)((const E*)p.dO + arow * DV + v0);
     static_assert(R::RO <= 1024, "a row of dO within the zero block");
-    dma_rows<R::RK, C, 4, true>(r + R::XK, Kg, (size_t)H * R::RK, len, Kg + (size_t)(len - 1) * H * R::RK, 0,
-                                prod, lane);
-    dma_rows<R::RO, C, 4, true>(r + R::XO, Og, (size_t)H * DV * sizeof(E), len, (const char*)p.wZ, 0, prod, lane);
-    if (prod < 3) dma4_asm(p.wb + gi * 3 * C + prod * C + lane, r + R::XG + prod * C * 4);
+    issue_keys(p.k, arow, len, r + R::XK);
+    if (len == C && ofit) dma_rows_full<R::RO, C, 4>(r + R::XO, Og, ostride, ooff, prod);
+    else dma_rows<R::RO, C, 4, true>(r + R::XO, Og, ostride, len, (const char*)p.wZ, 0, prod, lane);
+    if (prod < 3) dma4_base((const char*)(p.wb + gi * 3 * C + prod * C), 4 * lane, r + R::XG + prod * C * 4);
   };
   auto issueP = [&](int it) {
     size_t gi, arow;
     int len;
     chunk_at(nch - 1 - it, gi, arow, len);
-    dma_lbt<E, 4>(sm.ringP[it % R::NP], (const char*)((const E*)p.wP + gi * LBT_ELEMS), prod, lane);
+    dma_lbt<E, 4>(sm.ringP[it % R::NP], (const char*)((const E*)p.wP + gi * LBT_ELEMS), lbt, prod);
   };
   auto issueM = [&](int it) {
     size_t gi, arow;
     int len;
     chunk_at(nch - 1 - it, gi, arow, len);
-    dma_lbt<E, 4>(sm.ringM, (const char*)((const E*)p.wM + gi * LBT_ELEMS), prod, lane);
+    dma_lbt<E, 4>(sm.ringM, (const char*)((const E*)p.wM + gi * LBT_ELEMS), lbt, prod);
   };
 
   f4 acc[KPW][NBS];
@@ -599,7 +607,7 @@ __global__ __launch_bounds__(INTRA_THREADS) __attribute__((amdgpu_waves_per_eu(i
   zero_upper_chunks<E>(sm.Mm, tid, INTRA_THREADS);
   issue(0);
   {
-    dma_lbt<E, NWAVES>(sm.Mm, (const char*)((const E*)p.wP + gi * LBT_ELEMS), w, lane);
+    dma_lbt<E, NWAVES>(sm.Mm, (const char*)((const E*)p.wP + gi * LBT_ELEMS), LbtLane<E, NWAVES>(w, lane), w);
   }
   issue(1);
   static_assert(NVT % 2 == 0, "the last tile uses slot 1");
@@ -643,7 +651,7 @@ __global__ __launch_bounds__(INTRA_THREADS) __attribute__((amdgpu_waves_per_eu(i
     if (vt == NVT - 1) {
       // every wave is past its last read of P: M goes over it
       block_sync_lds();
-      dma_lbt<E, NWAVES>(sm.Mm, (const char*)((const E*)p.wM + gi * LBT_ELEMS), w, lane);
+      dma_lbt<E, NWAVES>(sm.Mm, (const char*)((const E*)p.wM + gi * LBT_ELEMS), LbtLane<E, NWAVES>(w, la), w);
     }
     products(t, la, WITHOUT_DD | WITH_DD);
   }

@@ -237,6 +237,24 @@ __device__ inline void dma16_asm(const void* g, char* lds) {
   const uint32_t base = __builtin_amdgcn_readfirstlane((uint32_t)(uintptr_t)lds);
   asm volatile("s_mov_b32 m0, %0\n\tglobal_load_lds_dwordx4 %1, off" ::"s"(base), "v"(g) : "memory", "m0");
 }
+// The same with a uniform base address and one 32-bit byte offset per lane: a
+// load then costs a wave no vector instruction but itself.
+template <typename T>
+__device__ inline const T* uniform_ptr(const T* p) {
+  const uint64_t a = (uint64_t)(uintptr_t)p;
+  const uint32_t lo = __builtin_amdgcn_readfirstlane((uint32_t)a), hi = __builtin_amdgcn_readfirstlane((uint32_t)(a >> 32));
+  return (const T*)(uintptr_t)(((uint64_t)hi << 32) | lo);
+}
+__device__ inline void dma16_base(const char* base, uint32_t off, char* lds) {
+  const uint32_t l = __builtin_amdgcn_readfirstlane((uint32_t)(uintptr_t)lds);
+  asm volatile("s_mov_b32 m0, %0\n\tglobal_load_lds_dwordx4 %1, %2" ::"s"(l), "v"(off), "s"(uniform_ptr(base))
+               : "memory", "m0");
+}
+__device__ inline void dma4_base(const char* base, uint32_t off, char* lds) {
+  const uint32_t l = __builtin_amdgcn_readfirstlane((uint32_t)(uintptr_t)lds);
+  asm volatile("s_mov_b32 m0, %0\n\tglobal_load_lds_dword %1, %2" ::"s"(l), "v"(off), "s"(uniform_ptr(base))
+               : "memory", "m0");
+}
 __device__ inline void dma4_asm(const void* g, char* lds) {
   const uint32_t base = __builtin_amdgcn_readfirstlane((uint32_t)(uintptr_t)lds);
   asm volatile("s_mov_b32 m0, %0\n\tglobal_load_lds_dword %1, off" ::"s"(base), "v"(g) : "memory", "m0");
@@ -267,6 +285,30 @@ __device__ inline void dma_rows(char* dst, const char* src, size_t stride, int v
   }
 }
 
+// dma_rows of a block whose rows are all valid, with the lane offset formed
+// once: the rows of a wave's successive instructions lie a multiple of 16
+// apart, so that their swizzle and lane offset are those of its first.  The
+// offset is 32 bits: rows_fit says whether ROWS rows lie within it.  (Producer
+// waves share their SIMDs with two compute waves each and come last there:
+// with 12 to 30 vector instructions of address per load, the loads of a chunk
+// of the forward scan took them 3100 of its 3900 cycles, and the compute waves
+// waited 500 + 450 for them.)
+template <int RB, int NW>
+__device__ inline uint32_t dma_off(size_t stride, int w, int lane) {
+  constexpr int NCH = RB / 16, RPI = 1024 / RB;
+  static_assert((NW * RPI) % 16 == 0, "same swizzle in every instruction of a wave");
+  const int row = w * RPI + lane / NCH, c = (lane % NCH) ^ tile_swz<RB>(row);
+  return (uint32_t)(row * stride + c * 16);
+}
+__device__ inline bool rows_fit(int rows, size_t stride) { return rows * stride < ((size_t)1 << 32); }
+template <int RB, int ROWS, int NW>
+__device__ inline void dma_rows_full(char* dst, const char* src, size_t stride, uint32_t off, int w) {
+  constexpr int RPI = 1024 / RB, NI = ROWS / RPI;
+  static_assert(NI % NW == 0, "instructions split evenly over the waves");
+#pragma unroll
+  for (int j = 0; j < NI / NW; ++j) dma16_base(src + (size_t)(j * NW * RPI) * stride, off, dst + (j * NW + w) * 1024);
+}
+
 // C x C operators whose 16 x 16 blocks above the diagonal are zero (P, M, T)
 // are stored packed: the ten blocks on and below the diagonal, block (r, c)
 // (c <= r) at index r (r + 1) / 2 + c, each row-major.  Stores then cover
@@ -281,21 +323,25 @@ __device__ inline int lbt_block(int br, int bc) { return br * (br + 1) / 2 + bc;
 // rows, whose first block is on or below the diagonal, so each has active
 // lanes and the outstanding-load count is that of a full tile.
 template <typename E, int NW>
-__device__ inline void dma_lbt(char* dst, const char* src, int w, int lane) {
-  constexpr int RB = C * (int)sizeof(E), NCH = RB / 16, RPI = 1024 / RB, NI = C / RPI;
-  constexpr int BCH = 16 * (int)sizeof(E) / 16;   // 16-byte chunks per block row
-  static_assert(NI % NW == 0, "instructions split evenly over the waves");
+struct LbtLane {
+  static constexpr int RB = C * (int)sizeof(E), NCH = RB / 16, RPI = 1024 / RB, NI = C / RPI;
+  static constexpr int BCH = 16 * (int)sizeof(E) / 16;   // 16-byte chunks per block row
+  static_assert(NI % NW == 0 && (NW * RPI) % 16 == 0, "instructions split evenly, same swizzle in each");
+  uint32_t off;                       // bytes from the first block of a block row
+  int bc;                             // block column
+  __device__ inline LbtLane(int w, int lane) {
+    const int row = w * RPI + lane / NCH, c = (lane % NCH) ^ tile_swz<RB>(row);
+    bc = c / BCH;
+    off = (uint32_t)((bc * 256 + (row & 15) * 16) * sizeof(E) + (c % BCH) * 16);
+  }
+};
+template <typename E, int NW>
+__device__ inline void dma_lbt(char* dst, const char* src, const LbtLane<E, NW>& l, int w) {
+  typedef LbtLane<E, NW> L;
 #pragma unroll
-  for (int j = 0; j < NI / NW; ++j) {
-    int l = lane;                     // formed again per instruction: no address kept live across them
-    asm volatile("" : "+v"(l));
-    const int i = j * NW + w;
-    const int row = i * RPI + l / NCH;
-    const int c = (l % NCH) ^ tile_swz<RB>(row);
-    const int br = row >> 4, bc = c / BCH;
-    if (bc <= br)
-      dma16_asm(src + ((size_t)lbt_block(br, bc) * 256 + (row & 15) * 16) * sizeof(E) + (c % BCH) * 16,
-                dst + i * 1024);
+  for (int j = 0; j < L::NI / NW; ++j) {
+    const int i = j * NW + w, br = (i * L::RPI) >> 4;   // block row: uniform
+    if (l.bc <= br) dma16_base(src + (size_t)lbt_block(br, 0) * 256 * sizeof(E), l.off, dst + i * 1024);
   }
 }
 

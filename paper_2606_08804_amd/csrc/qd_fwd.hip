@@ -527,15 +527,23 @@ __global__ __launch_bounds__(NCW * 64 + 256) void k_scan_fwd(Params p) {
     gi = (size_t)(base + c) * H + h;
     arow = (size_t)t0 * H + h;
   };
-  // producers: Q of chunk c (rows past the chunk re-read its last row: they
-  // only meet zero gates)
+  // lane offsets of the producers' loads within a chunk (dma_rows_full)
+  const size_t kstride = (size_t)H * R::RK;
+  const uint32_t koff = dma_off<R::RK, 4>(kstride, prod & 3, lane), voff = dma_off<R::RO, 4>(vstride, prod & 3, lane);
+  const LbtLane<E, 4> lbt(prod & 3, lane);
+  const bool kfit = rows_fit(C, kstride), vfit = rows_fit(C, vstride);
+  // rows past the chunk re-read its last row: they only meet zero gates
+  auto issue_keys = [&](const void* src, size_t arow, int len, char* dst) {
+    const char* g = (const char*)((const E*)src + arow * DK);
+    if (len == C && kfit) dma_rows_full<R::RK, C, 4>(dst, g, kstride, koff, prod);
+    else dma_rows<R::RK, C, 4, true>(dst, g, kstride, len, g + (size_t)(len - 1) * kstride, 0, prod, lane);
+  };
+  // producers: Q of chunk c
   auto issueQ = [&](int c) {
     size_t gi, arow;
     int len;
     chunk_at(c, gi, arow, len);
-    const char* Qg = (const char*)((const E*)p.q + arow * DK);
-    dma_rows<R::RK, C, 4, true>(sm.ringA[c % NA] + R::AQ, Qg, (size_t)H * R::RK, len,
-                                Qg + (size_t)(len - 1) * H * R::RK, 0, prod, lane);
+    issue_keys(p.q, arow, len, sm.ringA[c % NA] + R::AQ);
   };
   // producers: K and the gate block of chunk c
   auto issueK = [&](int c) {
@@ -543,10 +551,8 @@ __global__ __launch_bounds__(NCW * 64 + 256) void k_scan_fwd(Params p) {
     int len;
     chunk_at(c, gi, arow, len);
     char* r = sm.ringA[c % NA];
-    const char* Kg = (const char*)((const E*)p.k + arow * DK);
-    dma_rows<R::RK, C, 4, true>(r + R::AK, Kg, (size_t)H * R::RK, len, Kg + (size_t)(len - 1) * H * R::RK, 0,
-                                prod, lane);
-    if (prod < 3) dma4_asm(p.wb + gi * 3 * C + prod * C + lane, r + R::AG + prod * C * 4);
+    issue_keys(p.k, arow, len, r + R::AK);
+    if (prod < 3) dma4_base((const char*)(p.wb + gi * 3 * C + prod * C), 4 * lane, r + R::AG + prod * C * 4);
   };
   // producers: P of chunk c
   auto issueP = [&](int c) {
@@ -554,7 +560,7 @@ __global__ __launch_bounds__(NCW * 64 + 256) void k_scan_fwd(Params p) {
     size_t gi, arow;
     int len;
     chunk_at(c, gi, arow, len);
-    dma_lbt<E, 4>(sm.Pt[c % R::NP], (const char*)((const E*)p.wP + gi * LBT_ELEMS), prod, lane);
+    dma_lbt<E, 4>(sm.Pt[c % R::NP], (const char*)((const E*)p.wP + gi * LBT_ELEMS), lbt, prod);
   };
   // producers: T and this tile's columns of V of chunk c (rows of V past the
   // chunk re-read its last row: they only meet zero columns of T)
@@ -563,10 +569,13 @@ __global__ __launch_bounds__(NCW * 64 + 256) void k_scan_fwd(Params p) {
     int len;
     chunk_at(c, gi, arow, len);
     const char* Vg = (const char*)((const E*)p.v + arow * p.ldv + v0);
-    dma_lbt<E, 4>(sm.ringB + R::BT, (const char*)((const E*)p.wT + gi * LBT_ELEMS), prod, lane);
-    if (!map_tile)
-      dma_rows<R::RO, C, 4, true>(sm.ringB + R::BV_, Vg, vstride, len, Vg + (size_t)(len - 1) * vstride, 0, prod,
-                                  lane);
+    dma_lbt<E, 4>(sm.ringB + R::BT, (const char*)((const E*)p.wT + gi * LBT_ELEMS), lbt, prod);
+    if (!map_tile) {
+      if (len == C && vfit) dma_rows_full<R::RO, C, 4>(sm.ringB + R::BV_, Vg, vstride, voff, prod);
+      else
+        dma_rows<R::RO, C, 4, true>(sm.ringB + R::BV_, Vg, vstride, len, Vg + (size_t)(len - 1) * vstride, 0, prod,
+                                    lane);
+    }
   };
 
   // state: acc[i][j] = S^T rows 16 (kb0 + i).., columns 16 (ns0 + j).. of this tile
