@@ -103,7 +103,7 @@ def kernel_alg_bytes_per_token_head(stage, Dk, Dv, e, saved=True):
         return qk + v + gates + v
     if stage == "intra":                    # q, k, v, dO, gates, entry states -> dq, dk, dgates
         return qk + 2 * v + gates + states + qk + gates
-    if stage == "seg_maps":                 # q, k, v, gates (segment maps: hand-offs)
+    if stage == "seg_maps":                 # q, k, v, gates (segment maps: hand-offs; the first segment's o in seg_out)
         return qk + v + gates
     if stage == "seg_out":                  # q, k, v, gates -> o
         return qk + v + gates + v
@@ -711,7 +711,8 @@ def run_decode(args):
 def run_segments(args):
     """The segment-parallel forward against the single pass on long
     sequences: B=1, T=65536, d=128, bf16, at H = 16 (the long-context
-    workload), 4 and 2, for 1 (the single pass), 2, 4, 8 and 16 segments;
+    workload), 4 and 2, for 1 (the single pass), 2, 4, 8, 16 and the
+    suggested number of segments;
     `value` is the long-context workload with the library's suggested
     segment count."""
     T, d = 65536, 128
@@ -723,7 +724,7 @@ def run_segments(args):
         ins = (g["q"], g["k"], g["v"], g["beta"], g["lam"], g["log_alpha"], g["initial_state"])
         sugg = qdelta.suggest_segments(1, T, H, d, d)
         res = {}
-        for G in (1, 2, 4, 8, 16):
+        for G in sorted({1, 2, 4, 8, 16, sugg}):
             ws = torch.empty(qdelta.segmented_workspace_bytes(1, T, H, d, d, qdelta.QDELTA_BF16, G),
                              dtype=torch.uint8, device="cuda")
             ms, _, _ = timed(lambda: qdelta.chunk_fwd_segmented(*ins, n_segments=G, workspace=ws),

@@ -153,12 +153,13 @@ int qdelta_chunk_fwd(int32_t B, int32_t T, int32_t H, int32_t Dk, int32_t Dv, in
  * chunk acts on the state as an affine map S -> S A_c + B_c (Sec. 3.3, the
  * compact chunk update S' = S (g_C I - W^T Kbar) + U^T Kbar), so a run of
  * chunks is one too.  Each sequence is cut into segments of
- * ceil(ceil(T/chunk) / n_segments) chunks; every segment's map (A: Dk x Dk,
- * B: Dv x Dk) is formed in parallel from a zero state, the segments' entry
+ * ceil(ceil(T/chunk) / n_segments) chunks; the first is run from the
+ * initial state with its outputs while the map (A: Dk x Dk, B: Dv x Dk) of
+ * every other but the last is formed from a zero state; the segments' entry
  * states follow in order (S_{g+1} = S_g A_g + B_g, fp32), and every segment
- * is then run again from its entry state, writing its outputs.  About three
- * times the scan work of the single pass (A has Dk rows) for up to
- * n_segments times its parallelism.
+ * after the first is then run from its entry state, writing its outputs.
+ * Up to about three times the scan work of the single pass (A has Dk rows)
+ * for up to n_segments times its parallelism.
  *   Arguments as qdelta_chunk_fwd, plus n_segments >= 1 (1: the single
  *   pass); ws_bytes >= qdelta_segmented_workspace_bytes(..., n_segments).
  *   Results equal qdelta_chunk_fwd's up to rounding (not bit for bit: the

@@ -66,7 +66,8 @@ Layout make_layout(size_t units, int Dk, int Dv, int esz, bool bwd) {
 }
 
 // Segment-parallel forward: the forward layout, then each segment's map
-// (B and A rows, fp32) and each segment's entry state (fp32).
+// (B and A rows, fp32; the first and the last segment's are not used) and
+// each segment's entry state (fp32; the first's is not used).
 struct SegLayout {
   Layout fwd;
   size_t out = 0, in = 0, total = 0;
@@ -447,19 +448,40 @@ int32_t qdelta_suggest_segments(int32_t B, int32_t T, int32_t H, int32_t Dk, int
   if (B <= 0 || T <= 0 || H <= 0 || Dk <= 0 || Dv <= 0) return 1;
   const long long cus = qd::device_cu_count();
   const long long seq_heads = (long long)B * H;
-  const int NT = (T + C - 1) / C;
-  // the single pass runs one workgroup per (sequence, head, 32 value rows);
-  // with half as many of them as CUs or more it is the faster form
-  // (measured at B1 T65536 d128 bf16: 16 heads, 64 workgroups, take 1.64 ms
-  // in one pass and about 1.0 ms in eight segments)
-  if (seq_heads * (Dv / 32) * 2 >= cus) return 1;
-  // the maps pass runs (Dv + Dk) / w workgroups per segment (w = 64 value
-  // rows for bf16, 32 for fp32): up to two per CU, with segments of at least
-  // 16 chunks
-  const int w = dtype == QDELTA_BF16 ? 64 : 32;
-  int G = 1;
-  while (G < 16 && seq_heads * (2 * G) * ((Dv + Dk) / w) <= 2 * cus && NT / (2 * G) >= 16) G *= 2;
-  return G;
+  const long long NT = ((long long)T + C - 1) / C;
+  if (seq_heads > cus) return 1;             // the single pass fills the chip (and no product below overflows)
+  // The scans hold one workgroup per CU, dealt to the XCDs eight at a time,
+  // so a pass takes as many rounds as its fullest XCD has workgroups for its
+  // CUs, each as long as a segment.  The weights are the measured times of a
+  // chunk (tenths of a 32-row output tile's, 1.4 us at bf16 d 128 and 3.9 us
+  // at fp32), those of `setup` and `step` the fixed cost of the two extra
+  // launches and of composing one map.  Against the times at 65536 tokens,
+  // bf16 d 128: 16 heads 826 us in 5 segments, 833 in 9, 902 in 8, 1511 in
+  // one pass; 32 heads 1411 us in 3, 1705 in one pass; 4 heads 304 us in 16,
+  // 382 in 17, 1404 in one pass; 24 heads 1228 us in 6, 1313 in 3, 1618 in
+  // one pass.  At 32768 tokens, fp32, 8 heads of 64: 424 us in 17, 430 in 16,
+  // 526 in 9, 1353 in one pass.
+  const bool bf = dtype == QDELTA_BF16;
+  const int one = bf ? 10 : 7, map = bf ? 13 : 10, out = 10, out64 = 15, setup = 40, step = bf ? 30 : 5;
+  const int wm = bf ? 64 : 32;               // rows of a map tile
+  using qd::on_xcd;
+  using qd::xcd_rounds;
+  int best = 1;
+  long long best_cost = NT * one * xcd_rounds(on_xcd(seq_heads, (Dv + 31) / 32));
+  // segments of at least 6 chunks (63 chunks, 2 heads of 64: 42 us in
+  // segments of 7, 44 of 8, 78 in one pass), and at most 32 of them
+  for (int G = 2; G <= 32 && NT / G >= 6; ++G) {
+    const long long L = (NT + G - 1) / G, outs = seq_heads * (G - 1);
+    const bool wide = bf && qd::seg_out_wide(outs, Dv);
+    const long long r1 = xcd_rounds(on_xcd(seq_heads, (Dv + 31) / 32) + on_xcd(seq_heads * (G - 2), (Dv + Dk) / wm));
+    const long long r2 = xcd_rounds(on_xcd(outs, wide ? Dv / 64 : (Dv + 31) / 32));
+    const long long cost = L * (r1 * map + r2 * (wide ? out64 : out)) + setup + (long long)step * (G - 2);
+    if (cost < best_cost) {
+      best_cost = cost;
+      best = G;
+    }
+  }
+  return best;
 }
 
 int qdelta_chunk_fwd_segmented(int32_t B, int32_t T, int32_t H, int32_t Dk, int32_t Dv, int32_t chunk,

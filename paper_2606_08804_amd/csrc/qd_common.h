@@ -492,8 +492,8 @@ struct Params {
   // segments of seg_chunks chunks
   int n_seg;
   int seg_chunks;
-  float* wSegOut;        // [N*H][n_seg][Dv + Dk][Dk] fp32: each segment's B (value rows) and A (map rows)
-  float* wSegIn;         // [N*H][n_seg][Dv][Dk] fp32: each segment's entry state
+  float* wSegOut;        // [N*H][n_seg][Dv + Dk][Dk] fp32: B (value rows) and A (map rows) of all segments but the first and last
+  float* wSegIn;         // [N*H][n_seg][Dv][Dk] fp32: entry state of each segment but the first
 };
 
 // Token range of sequence n; false when cu_seqlens is malformed for n.

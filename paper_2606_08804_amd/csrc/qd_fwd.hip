@@ -459,16 +459,23 @@ struct alignas(16) ScanFwdSmem {
 // affine map S -> S A + B of the state, Sec. 3.3 compact chunk update, and so
 // is a segment):
 //   SEG_NONE  one workgroup walks the whole sequence (the single pass);
+//   SEG_FIRST the first segment from the initial state with every output; it
+//             ends at the second segment's entry state, in p.wSegIn;
 //   SEG_MAPS  per segment from a zero state, no outputs: the value tiles end
 //             at the segment's B, and DK / BV extra tiles whose rows start as
 //             rows of the identity and see no values (their V product is
 //             skipped) end at the rows of its A; both go to p.wSegOut;
 //   SEG_OUT   per segment from its entry state in p.wSegIn, with every
 //             output; the last segment writes the final state.
-enum { SEG_NONE = 0, SEG_MAPS = 1, SEG_OUT = 2 };
+// The first segment needs no map (its entry state is given) and nothing
+// follows the last, so SEG_MAPS runs for the segments between them, in one
+// launch with SEG_FIRST (k_scan_seg), and SEG_OUT for all but the first.
+enum { SEG_NONE = 0, SEG_MAPS = 1, SEG_OUT = 2, SEG_FIRST = 3 };
 
+// The scan of value tile vt of segment g (0 in the single pass) of sequence
+// and head `unit`.
 template <typename E, int DK, int DV, int BV, int NCW, int SEG>
-__global__ __launch_bounds__(NCW * 64 + 256) void k_scan_fwd(Params p) {
+__device__ __forceinline__ void scan_fwd_tile(const Params& p, ScanFwdSmem<E, DK, BV>& sm, int unit, int g, int vt) {
   constexpr int P = Pad<E>::v;
   constexpr int LK = DK + P, LV = BV + P;
   constexpr int NVT = DV / BV;
@@ -495,7 +502,6 @@ __global__ __launch_bounds__(NCW * 64 + 256) void k_scan_fwd(Params p) {
   constexpr bool MAPS = SEG == SEG_MAPS;
   static_assert(!MAPS || (NA == 2 && R::NP == 1), "the maps pass runs the two-deep ring with one P buffer");
   constexpr int LT = C * R::RC / 1024 / 4;    // loads per producer: T alone
-  __shared__ ScanFwdSmem<E, DK, BV> sm;
   const int tid = threadIdx.x, lane = tid & 63, w = wave_id(tid);
   const int prod = w - NCW;                   // 0-3 for the producer waves, negative otherwise
   const bool producer = prod >= 0;
@@ -503,10 +509,7 @@ __global__ __launch_bounds__(NCW * 64 + 256) void k_scan_fwd(Params p) {
   const int kb0 = (w % (NCW / SG)) * KPW, ns0 = (w / (NCW / SG)) * NBS;
   constexpr int G = SEG == SEG_NONE ? 1 : 0;          // 0: the run-time segment count
   const int nseg = G ? G : p.n_seg;
-  constexpr int NTILE = NVT + (SEG == SEG_MAPS ? DK / BV : 0);
-  int su, vt;
-  if (!xcd_unit_tile(blockIdx.x, p.N * p.H * nseg, NTILE, su, vt)) return;
-  const int unit = G ? su : su / nseg, g = G ? 0 : su % nseg;
+  const int su = unit * nseg + g;
   const bool map_tile = SEG == SEG_MAPS && vt >= NVT;  // rows of the segment's A (no values)
   const int H = p.H, n = unit / H, h = unit % H;
   const size_t vstride = (size_t)H * p.ldv * ES;       // bytes from one token's row of V to the next
@@ -585,7 +588,7 @@ __global__ __launch_bounds__(NCW * 64 + 256) void k_scan_fwd(Params p) {
 #pragma unroll
     for (int j = 0; j < NBS; ++j) {
       const int kt = kb0 + i, nb = ns0 + j;
-      if constexpr (SEG == SEG_NONE) {
+      if constexpr (SEG == SEG_NONE || SEG == SEG_FIRST) {
         acc[i][j] = (p.S0 && !producer)
                         ? *(const f4*)(p.S0 + ((size_t)unit * DV + v0 + nb * 16 + fcol(lane)) * DK + kt * 16 +
                                        frow(lane, 0))
@@ -839,6 +842,16 @@ __global__ __launch_bounds__(NCW * 64 + 256) void k_scan_fwd(Params p) {
           *(f4*)(p.wSegOut + ((size_t)su * (DV + DK) + r0 + nb * 16 + fcol(lane)) * DK + kt * 16 +
                  frow(lane, 0)) = acc[i][j];
         }
+    } else if (SEG == SEG_FIRST) {
+      // the second segment's entry state
+#pragma unroll
+      for (int i = 0; i < KPW; ++i)
+#pragma unroll
+        for (int j = 0; j < NBS; ++j) {
+          const int kt = kb0 + i, nb = ns0 + j;
+          *(f4*)(p.wSegIn + ((size_t)(su + 1) * DV + v0 + nb * 16 + fcol(lane)) * DK + kt * 16 + frow(lane, 0)) =
+              acc[i][j];
+        }
     } else if (p.Sfin && (SEG == SEG_NONE || g == nseg - 1)) {
 #pragma unroll
       for (int i = 0; i < KPW; ++i)
@@ -849,6 +862,52 @@ __global__ __launch_bounds__(NCW * 64 + 256) void k_scan_fwd(Params p) {
               acc[i][j];
         }
     }
+  }
+}
+
+template <typename E, int DK, int DV, int BV, int NCW, int SEG>
+__global__ __launch_bounds__(NCW * 64 + 256) void k_scan_fwd(Params p) {
+  __shared__ ScanFwdSmem<E, DK, BV> sm;
+  const int nseg = SEG == SEG_OUT ? p.n_seg - 1 : 1;   // SEG_OUT: every segment but the first
+  int su, vt;
+  if (!xcd_unit_tile(blockIdx.x, p.N * p.H * nseg, DV / BV, su, vt)) return;
+  const int unit = SEG == SEG_OUT ? su / nseg : su, g = SEG == SEG_OUT ? 1 + su % nseg : 0;
+  scan_fwd_tile<E, DK, DV, BV, NCW, SEG>(p, sm, unit, g, vt);
+}
+
+// Workgroups of the first segments in k_scan_seg (a multiple of 8, so that
+// those of the maps start on XCD 0 again) and of the maps.
+constexpr int SEG_FIRST_BV = 32;
+__host__ __device__ inline int seg_first_blocks(int units, int Dv) { return (units + 7) / 8 * 8 * (Dv / SEG_FIRST_BV); }
+template <int DK, int DV, int BV>
+__host__ __device__ inline int seg_map_blocks(int units, int n_seg) {
+  return (units * (n_seg - 2) + 7) / 8 * 8 * ((DV + DK) / BV);
+}
+
+// First pass of the segment-parallel forward: the first segments with their
+// outputs, and the maps of those between the first and the last.  The first
+// segments take 32-row tiles (1.4 us a chunk at bf16 d 128; a map's 64-row
+// tile 1.8, an output tile of 64 rows 2.1): they do more per chunk than a map
+// and would otherwise end last.  Without the first segment's map, the last
+// one's and the first's second walk, a segment less is walked in the outputs
+// pass and two less here: 65536 tokens, 16 heads, bf16 d 128, 893 us in 8
+// segments with all of them, 826 us in 5 without.
+template <typename E, int DK, int DV, int BV, int NCW>
+__global__ __launch_bounds__(NCW * 64 + 256) void k_scan_seg(Params p) {
+  union Smem {
+    ScanFwdSmem<E, DK, SEG_FIRST_BV> first;
+    ScanFwdSmem<E, DK, BV> map;
+  };
+  __shared__ Smem sm;
+  const int units = p.N * p.H, nf = seg_first_blocks(units, DV);
+  int su, vt;
+  if ((int)blockIdx.x < nf) {
+    if (!xcd_unit_tile(blockIdx.x, units, DV / SEG_FIRST_BV, su, vt)) return;
+    scan_fwd_tile<E, DK, DV, SEG_FIRST_BV, NCW, SEG_FIRST>(p, sm.first, su, 0, vt);
+  } else {
+    const int nmap = p.n_seg - 2;
+    if (!xcd_unit_tile(blockIdx.x - nf, units * nmap, (DV + DK) / BV, su, vt)) return;
+    scan_fwd_tile<E, DK, DV, BV, NCW, SEG_MAPS>(p, sm.map, su / nmap, 1 + su % nmap, vt);
   }
 }
 
@@ -888,9 +947,9 @@ static hipError_t launch_fwd_t(const Params& p, int in_bwd, int with_scan, hipSt
   return hipGetLastError();
 }
 
-// Entry states of the segments of every (sequence, head): S_0 = the initial
-// state (or zero), S_{g+1} = S_g A_g + B_g with segment g's map from the
-// SEG_MAPS pass, in fp32.  One workgroup per (sequence, head, 8 value rows)
+// Entry states of the segments of every (sequence, head) from the third on:
+// S_1 is where the first segment ended, S_{g+1} = S_g A_g + B_g with segment
+// g's map from the SEG_MAPS pass, in fp32.  One workgroup per (sequence, head, 8 value rows)
 // walks the segments in order: each step stages A_g in LDS (coalesced
 // 16-byte loads, issued one step ahead so that their latency overlaps the
 // previous step), then every thread forms one column of its rows from LDS.
@@ -923,15 +982,15 @@ __global__ __launch_bounds__(NTHREADS) void k_seg_compose(Params p) {
 #pragma unroll
   for (int m = 0; m < RPT; ++m) {
     const int v = rb * RB + rsub + m * TPR;
-    cur[m] = p.S0 ? p.S0[((size_t)unit * DV + v) * DK + k] : 0.f;
+    cur[m] = p.wSegIn[(((size_t)unit * G + 1) * DV + v) * DK + k];
   }
-  if (G > 1) fetch(0);
-  for (int g = 0; g < G; ++g) {
+  if (G > 2) fetch(1);
+  for (int g = 1; g < G; ++g) {
     const size_t su = (size_t)unit * G + g;
 #pragma unroll
     for (int m = 0; m < RPT; ++m) {
       const int v = rb * RB + rsub + m * TPR;
-      p.wSegIn[(su * DV + v) * DK + k] = cur[m];
+      if (g > 1) p.wSegIn[(su * DV + v) * DK + k] = cur[m];
       Srow[rsub + m * TPR][k] = cur[m];
     }
     if (g + 1 == G) break;
@@ -955,12 +1014,13 @@ __global__ __launch_bounds__(NTHREADS) void k_seg_compose(Params p) {
   }
 }
 
-// Segment-parallel forward (dense batch): preparation, the maps of every
-// segment (from zero), their composition into segment entry states, and the
-// outputs pass of every segment from its entry state.  The maps pass takes
-// the widest value tiles (it has (DV + DK) / BV of them per segment, and
+// Segment-parallel forward (dense batch): preparation; the first segments
+// with the maps of those between first and last (from zero); the maps'
+// composition into segment entry states; and the outputs pass of every
+// segment after the first from its entry state.  The maps take
+// the widest value tiles (there are (DV + DK) / BV of them per segment, and
 // wider tiles re-read the operands their segment shares fewer times); the
-// outputs pass takes them too once they still give every CU a workgroup.
+// outputs pass takes them where they save rounds (seg_out_wide).
 template <typename E, int DK, int DV>
 static hipError_t launch_fwd_seg_t(const Params& p, hipStream_t st) {
   hipError_t e = launch_fwd_t<E, DK, DV>(p, 0, 0, st);    // preparation only
@@ -969,21 +1029,23 @@ static hipError_t launch_fwd_seg_t(const Params& p, hipStream_t st) {
   if (units == 0) return hipSuccess;
   constexpr int NCW = 8;
   constexpr int BW = scan_bv_max<E, DV>();     // 64 for bf16, else 32
-  const int su8 = ((units * p.n_seg + 7) / 8) * 8;
-  const bool out_wide = BW == 64 && (long long)units * p.n_seg * (DV / 64) >= device_cu_count();
+  const int outs = units * (p.n_seg - 1), out8 = (outs + 7) / 8 * 8;
+  const bool out_wide = BW == 64 && seg_out_wide(outs, DV);
   prof_mark(ST_SEG_MAPS, 0, st);
-  hipLaunchKernelGGL((k_scan_fwd<E, DK, DV, BW, NCW, SEG_MAPS>), dim3(su8 * (DV + DK) / BW),
+  hipLaunchKernelGGL((k_scan_seg<E, DK, DV, BW, NCW>),
+                     dim3(seg_first_blocks(units, DV) + seg_map_blocks<DK, DV, BW>(units, p.n_seg)),
                      dim3(NCW * 64 + 256), 0, st, p);
   prof_mark(ST_SEG_MAPS, 1, st);
   prof_mark(ST_SEG_COMPOSE, 0, st);
-  hipLaunchKernelGGL((k_seg_compose<DK, DV>), dim3(units * (DV / SEG_COMPOSE_RB)), dim3(NTHREADS), 0, st, p);
+  if (p.n_seg > 2)
+    hipLaunchKernelGGL((k_seg_compose<DK, DV>), dim3(units * (DV / SEG_COMPOSE_RB)), dim3(NTHREADS), 0, st, p);
   prof_mark(ST_SEG_COMPOSE, 1, st);
   prof_mark(ST_SEG_OUT, 0, st);
   if (out_wide)
-    hipLaunchKernelGGL((k_scan_fwd<E, DK, DV, BW, NCW, SEG_OUT>), dim3(su8 * DV / BW), dim3(NCW * 64 + 256), 0,
+    hipLaunchKernelGGL((k_scan_fwd<E, DK, DV, BW, NCW, SEG_OUT>), dim3(out8 * DV / BW), dim3(NCW * 64 + 256), 0,
                        st, p);
   else
-    hipLaunchKernelGGL((k_scan_fwd<E, DK, DV, 32, NCW, SEG_OUT>), dim3(su8 * DV / 32), dim3(NCW * 64 + 256), 0,
+    hipLaunchKernelGGL((k_scan_fwd<E, DK, DV, 32, NCW, SEG_OUT>), dim3(out8 * DV / 32), dim3(NCW * 64 + 256), 0,
                        st, p);
   prof_mark(ST_SEG_OUT, 1, st);
   return hipGetLastError();

@@ -38,6 +38,23 @@ hipError_t launch_fwd(const Params& p, int dtype, int Dk, int Dv, int in_bwd, in
 // segment maps, composition, outputs.
 hipError_t launch_fwd_seg(const Params& p, int dtype, int Dk, int Dv, hipStream_t st);
 
+// Workgroups of the fullest XCD when `units` are dealt to the eight XCDs
+// with `tiles` workgroups each, and the rounds that many take at one
+// workgroup per CU.
+inline long long on_xcd(long long units, int tiles) { return (units + 7) / 8 * tiles; }
+inline long long xcd_rounds(long long wgs) {
+  const long long cus = device_cu_count() / 8 > 0 ? device_cu_count() / 8 : 1;
+  return (wgs + cus - 1) / cus;
+}
+// Whether the outputs pass over `outs` segments takes 64-row tiles: a round
+// of them takes 1.5 times one of 32-row tiles (2.1 us a chunk against 1.4 at
+// bf16 d 128).  65536 tokens, 16 heads, 8 segments: 64-row tiles in one round
+// 901 us for the call, 32-row tiles in two 985; 5 segments: 32-row tiles, one
+// round either way.
+inline bool seg_out_wide(long long outs, int Dv) {
+  return 3 * xcd_rounds(on_xcd(outs, Dv / 64)) < 2 * xcd_rounds(on_xcd(outs, Dv / 32));
+}
+
 // Backward once the saved context (states, D, b, W, P, M) is in place:
 // reverse state scan, then the intra-chunk gradient kernel.
 hipError_t launch_bwd(const Params& p, int dtype, int Dk, int Dv, hipStream_t st);

@@ -157,6 +157,20 @@ def test_segmented_forward_sizes_and_validation():
     assert qdelta.suggest_segments(1, 65536, 2, 128, 128) > 1
 
 
+@pytest.mark.parametrize("dtype", [0, 1])
+def test_suggested_segments_range(dtype):
+    """The suggestion stays within 1 and 32 segments of at least 6 chunks, is
+    the single pass for sequences of under 12 chunks or more (sequence,
+    head) pairs than CUs, and holds at the largest sizes."""
+    for T in (1, 64, 704, 769, 4000, 8191, 65536, 2**31 - 1):
+        for H in (1, 2, 5, 16, 24, 33, 257):
+            G = qdelta.suggest_segments(1, T, H, 64, 128, dtype)
+            assert 1 <= G <= 32
+            assert G == 1 or -(-T // 64) // G >= 6, (T, H, G)
+    assert qdelta.suggest_segments(1, 704, 1, 64, 64, dtype) == 1
+    assert qdelta.suggest_segments(2**31 - 1, 2**31 - 1, 2**31 - 1, 128, 128, 1) == 1
+
+
 def test_recurrent_bwd_sizes_and_validation():
     L = qdelta.lib()
     E = qdelta

@@ -76,6 +76,25 @@ def test_segmented_long_context_full(gate):
     assert normwise(f64(Sf[:, heads].cpu()), S_ref) <= TOL["bf16"]
 
 
+@pytest.mark.parametrize("B,T,H,Dk,Dv,dt,G", [
+    (1, 300, 3, 128, 128, "bf16", 2),       # first and last only: no map to compose
+    (1, 385, 17, 64, 64, "bf16", 3),        # one map; heads that do not fill the XCDs
+    (2, 448, 32, 64, 128, "bf16", 3),       # 256 output tiles of 64 rows
+    (1, 449, 5, 64, 256, "f32", 8),         # one chunk each, the last of one token
+])
+def test_segmented_first_segment(B, T, H, Dk, Dv, dt, G):
+    """The first segment is the single pass over its tokens (the same tiles,
+    so bit for bit), and the others continue it."""
+    d = synth.make(B, T, H, Dk, Dv, dt, "G3", seed=177, s0=True)
+    o, Sf, _ = seg_fwd(d, G)
+    e = fwd_errors(d, o, Sf)
+    assert all(v <= TOL[dt] for v in e.values()), e
+    if dt == "bf16" and B * H * (Dv // 32) <= 256:
+        o1, _, _ = gpu_fwd(d)
+        n = -(-(-(-T // 64)) // G) * 64
+        assert torch.equal(o[:, :n], o1[:, :n])
+
+
 def test_segmented_empty_inputs():
     """T = 0 passes the initial state through; B = 0 launches nothing."""
     d = synth.make(2, 0, 2, 128, 128, "bf16", "G2", seed=175, s0=True)
