@@ -35,6 +35,7 @@ class QDeltaFunction(torch.autograd.Function):
 
     @staticmethod
     def forward(ctx, q, k, v, beta, lam, log_alpha, initial_state, cu_seqlens):
+        ctx.set_materialize_grads(False)         # an unused final state has no gradient: none is filled or read
         need = any(ctx.needs_input_grad[:7])
         o, final_state, saved = _binding.chunk_fwd(
             q, k, v, beta, lam, log_alpha, initial_state, cu_seqlens=cu_seqlens,

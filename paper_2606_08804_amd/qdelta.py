@@ -145,14 +145,25 @@ def _dt(t):
 
 
 def _p(t):
-    return None if t is None else ctypes.c_void_p(t.data_ptr())
+    return None if t is None else t.data_ptr()
+
+
+# The calls of one token or a short sequence are bound by this module's own
+# time.  Asking for the stream's handle without a Stream object takes 0.2 us
+# instead of 2.9.
+_raw_stream = getattr(torch._C, "_cuda_getCurrentRawStream", None)
 
 
 def _stream():
-    return ctypes.c_void_p(torch.cuda.current_stream().cuda_stream)
+    if _raw_stream is None:
+        return torch.cuda.current_stream().cuda_stream
+    return _raw_stream(torch.cuda.current_device())
 
 
 def _need(t, name, dtype=None, shape=None):
+    if (t is not None and t.is_cuda and t.is_contiguous() and (dtype is None or t.dtype == dtype)
+            and (shape is None or t.shape == shape)):
+        return t
     if t is None:
         raise ValueError(f"{name} is required")
     if not t.is_cuda:
