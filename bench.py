@@ -579,7 +579,8 @@ def run_recurrent(args):
     ms, avg_s, ms_chunk, ms_tr, avg_b, ms_ctr = main
     T = T_main
     # ALU roofline: forward 6 Dk Dv flops per token-head (S x and S q dot
-    # products, rank-1 update); backward 22 Dk Dv (three sweeps: 6 + 8 + 8)
+    # products, rank-1 update); backward 22 Dk Dv (the same token by token:
+    # recomputed states 6, adjoint 8, gradients 8)
     flops = B * T * H * 6 * d * d
     bflops = B * T * H * 22 * d * d
     kern = {"rec_fwd": {"avg_launch_us": avg_s * 1e6, "alg_flops_per_launch": flops,
