@@ -76,6 +76,20 @@ def test_layer_gradcheck(oracle_core, use_decay, fixed_lambda):
                                     eps=1e-6, atol=1e-7, rtol=1e-6)
 
 
+@pytest.mark.parametrize("used", [0, 1])
+def test_function_with_one_output_used(oracle_core, used):
+    """A loss on the outputs alone or on the final state alone: the other
+    output has no gradient, which equals a gradient of zeros."""
+    xs = [x.requires_grad_() for x in _inputs(1, 7, 2, 3, 4, seed=5)]
+    w = torch.randn(1, generator=torch.Generator().manual_seed(6), dtype=torch.float64)
+    outs = layer.qdelta_chunk(*xs)
+    got = torch.autograd.grad((w * outs[used] ** 2).sum(), xs)
+    outs = layer.qdelta_chunk(*xs)
+    want = torch.autograd.grad((w * outs[used] ** 2).sum() + 0.0 * outs[1 - used].sum(), xs)
+    for a, b in zip(got, want):
+        torch.testing.assert_close(a, b, rtol=0, atol=1e-14)
+
+
 def test_lambda_gate_at_initialisation():
     """lambda = sigmoid(W_lambda h + b), b a scalar initialised to -0.8: at
     h = 0 every head's lambda is sigmoid(-0.8); beta = 1/2; alpha = 1/2."""
