@@ -228,14 +228,16 @@ __device__ inline int tile_off(int row, int byte) {
 // cannot prove disjoint); every consumer must be ordered by an explicit
 // vmcnt wait in the issuing wave plus a barrier.  m0 holds the LDS base;
 // kernels using this form issue no compiler-generated direct loads, the only
-// other user of m0 here.
+// other user of m0 here.  A direct load may take m0 one wait state after its
+// write at the earliest; the compiler does not look into the text, so the wait
+// stands in it.
 #pragma clang diagnostic push
 #pragma clang diagnostic ignored "-Winline-asm"
 __device__ inline void dma16_asm(const void* g, char* lds) {
   // a generic pointer into LDS holds the LDS byte address in its low 32 bits;
   // the address is uniform across the wave (callers pass per-wave bases)
   const uint32_t base = __builtin_amdgcn_readfirstlane((uint32_t)(uintptr_t)lds);
-  asm volatile("s_mov_b32 m0, %0\n\tglobal_load_lds_dwordx4 %1, off" ::"s"(base), "v"(g) : "memory", "m0");
+  asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, off" ::"s"(base), "v"(g) : "memory", "m0");
 }
 // The same with a uniform base address and one 32-bit byte offset per lane: a
 // load then costs a wave no vector instruction but itself.
@@ -247,17 +249,17 @@ __device__ inline const T* uniform_ptr(const T* p) {
 }
 __device__ inline void dma16_base(const char* base, uint32_t off, char* lds) {
   const uint32_t l = __builtin_amdgcn_readfirstlane((uint32_t)(uintptr_t)lds);
-  asm volatile("s_mov_b32 m0, %0\n\tglobal_load_lds_dwordx4 %1, %2" ::"s"(l), "v"(off), "s"(uniform_ptr(base))
+  asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2" ::"s"(l), "v"(off), "s"(uniform_ptr(base))
                : "memory", "m0");
 }
 __device__ inline void dma4_base(const char* base, uint32_t off, char* lds) {
   const uint32_t l = __builtin_amdgcn_readfirstlane((uint32_t)(uintptr_t)lds);
-  asm volatile("s_mov_b32 m0, %0\n\tglobal_load_lds_dword %1, %2" ::"s"(l), "v"(off), "s"(uniform_ptr(base))
+  asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dword %1, %2" ::"s"(l), "v"(off), "s"(uniform_ptr(base))
                : "memory", "m0");
 }
 __device__ inline void dma4_asm(const void* g, char* lds) {
   const uint32_t base = __builtin_amdgcn_readfirstlane((uint32_t)(uintptr_t)lds);
-  asm volatile("s_mov_b32 m0, %0\n\tglobal_load_lds_dword %1, off" ::"s"(base), "v"(g) : "memory", "m0");
+  asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dword %1, off" ::"s"(base), "v"(g) : "memory", "m0");
 }
 #pragma clang diagnostic pop
 
