@@ -240,7 +240,11 @@ __device__ inline void dma16_asm(const void* g, char* lds) {
   asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, off" ::"s"(base), "v"(g) : "memory", "m0");
 }
 // The same with a uniform base address and one 32-bit byte offset per lane: a
-// load then costs a wave no vector instruction but itself.
+// load then costs a wave no vector instruction but itself.  Where the compiler
+// cannot prove the base uniform it takes it through v_readfirstlane, and a
+// vector instruction's write of a scalar register has to lie five wait states
+// before a memory instruction that reads it; s_nop 4 holds that for any order
+// of the instructions before the text, and m0's wait with it.
 template <typename T>
 __device__ inline const T* uniform_ptr(const T* p) {
   const uint64_t a = (uint64_t)(uintptr_t)p;
@@ -249,12 +253,12 @@ __device__ inline const T* uniform_ptr(const T* p) {
 }
 __device__ inline void dma16_base(const char* base, uint32_t off, char* lds) {
   const uint32_t l = __builtin_amdgcn_readfirstlane((uint32_t)(uintptr_t)lds);
-  asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2" ::"s"(l), "v"(off), "s"(uniform_ptr(base))
+  asm volatile("s_mov_b32 m0, %0\n\ts_nop 4\n\tglobal_load_lds_dwordx4 %1, %2" ::"s"(l), "v"(off), "s"(uniform_ptr(base))
                : "memory", "m0");
 }
 __device__ inline void dma4_base(const char* base, uint32_t off, char* lds) {
   const uint32_t l = __builtin_amdgcn_readfirstlane((uint32_t)(uintptr_t)lds);
-  asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dword %1, %2" ::"s"(l), "v"(off), "s"(uniform_ptr(base))
+  asm volatile("s_mov_b32 m0, %0\n\ts_nop 4\n\tglobal_load_lds_dword %1, %2" ::"s"(l), "v"(off), "s"(uniform_ptr(base))
                : "memory", "m0");
 }
 __device__ inline void dma4_asm(const void* g, char* lds) {

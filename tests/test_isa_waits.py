@@ -50,3 +50,28 @@ def test_m0_write_before_direct_load(kernels):
     """One wait state between a scalar write of M0 (the LDS base) and the load that takes it."""
     bad = {name for name, code, i in _direct_loads(kernels) if re.match(r"\S+ m0,", code[i - 1])}
     assert not bad, (len(bad), sorted(bad)[:3])
+
+
+def _sgprs(operand):
+    pair = re.match(r"s\[(\d+):(\d+)\]$", operand)
+    if pair:
+        return set(range(int(pair[1]), int(pair[2]) + 1))
+    one = re.match(r"s(\d+)$", operand)
+    return {int(one[1])} if one else set()
+
+
+def test_vector_write_before_scalar_base(kernels):
+    """Five wait states between a vector instruction's write of a scalar register (v_readfirstlane, v_readlane, a
+    compare) and a direct load with that register in its base address."""
+    bad = {}
+    for name, code, i in _direct_loads(kernels):
+        base = set().union(*(_sgprs(op.strip(",")) for op in code[i].split()[1:]))
+        states, j = 0, i - 1
+        while base and j >= 0 and states < 5:
+            parts = code[j].split()
+            if parts[0].startswith("v_") and len(parts) > 1 and _sgprs(parts[1].strip(",")) & base:
+                bad.setdefault(name, []).append((code[j], code[i], states))
+                break
+            states += _states(code[j])
+            j -= 1
+    assert not bad, (sum(map(len, bad.values())), sorted(bad), next(iter(bad.values()))[0])
