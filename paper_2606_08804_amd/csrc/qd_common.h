@@ -75,13 +75,10 @@ template <typename E> struct Pad { static constexpr int v = 16 / sizeof(E); };
 
 // ----------------------------------------------------------------- operand views
 // KMaj: element (i, k) at p[i*ld + k]   (k contiguous)
-// IMaj: element (i, k) at p[k*ld + i]   (i contiguous)
 // "i" is the row of an A operand or the column of a B operand.
 template <typename S> struct KMaj { const S* p; int ld; };
-template <typename S> struct IMaj { const S* p; int ld; };
 
 template <typename S> __device__ inline KMaj<S> kmaj(const S* p, int ld) { return KMaj<S>{p, ld}; }
-template <typename S> __device__ inline IMaj<S> imaj(const S* p, int ld) { return IMaj<S>{p, ld}; }
 
 template <typename E> struct Frag;
 
@@ -97,37 +94,13 @@ template <> struct Frag<__bf16> {
     r[4] = (__bf16)b[0]; r[5] = (__bf16)b[1]; r[6] = (__bf16)b[2]; r[7] = (__bf16)b[3];
     return r;
   }
-  template <typename S>
-  __device__ static inline bf8 load(IMaj<S> v, int i0, int k0, int lane) {
-    const S* s = v.p + (size_t)(k0 + (lane >> 4) * 8) * v.ld + i0 + (lane & 15);
-    bf8 r;
-#pragma unroll
-    for (int j = 0; j < 8; ++j) r[j] = (__bf16)tof(s[(size_t)j * v.ld]);
-    return r;
-  }
 };
 
 template <> struct Frag<float> {
   __device__ static inline f4 load(KMaj<float> v, int i0, int k0, int lane) {
     return *(const f4*)(v.p + (size_t)(i0 + (lane & 15)) * v.ld + k0 + (lane >> 4) * 4);
   }
-  __device__ static inline f4 load(IMaj<float> v, int i0, int k0, int lane) {
-    const float* s = v.p + (size_t)(k0 + (lane >> 4) * 4) * v.ld + i0 + (lane & 15);
-    f4 r;
-#pragma unroll
-    for (int j = 0; j < 4; ++j) r[j] = s[(size_t)j * v.ld];
-    return r;
-  }
 };
-
-// acc += A[m0:m0+16, 0:K] * B[0:K, n0:n0+16]
-template <typename E, int K, typename AV, typename BV>
-__device__ inline f4 mma_k(AV a, BV b, int m0, int n0, f4 acc, int lane) {
-#pragma unroll
-  for (int k0 = 0; k0 < K; k0 += Mma<E>::KS)
-    acc = Mma<E>::mma(Frag<E>::load(a, m0, k0, lane), Frag<E>::load(b, n0, k0, lane), acc);
-  return acc;
-}
 
 __device__ inline f4 zero4() { return f4{0.f, 0.f, 0.f, 0.f}; }
 

@@ -151,8 +151,16 @@ __global__ __launch_bounds__(PREP_THREADS) __attribute__((amdgpu_waves_per_eu(pr
 #pragma unroll
     for (int j = 0; j < 4; ++j) dst[frow(lane, j) * LB + fcol(lane)] = sc * v[j];
   };
+  // products of 16 x 16 blocks, their sums in ascending order of k (instruction
+  // j takes k = 4 j .. 4 j + 3; 16-byte fragments would take 0, 4, 8, 12 first):
+  // without decay the state keeps every bf16 rounding of T that another order
+  // of these sums flips
   auto prod = [&](const float* a, const float* m, f4 acc) {
-    return mma_k<float, 16>(kmaj(a, LB), imaj(m, LB), 0, 0, acc, lane);
+    const int g = lane >> 4, l = lane & 15;
+#pragma unroll
+    for (int j = 0; j < 4; ++j)
+      acc = __builtin_amdgcn_mfma_f32_16x16x4f32(a[l * LB + 4 * j + g], m[(4 * j + g) * LB + l], acc, 0, 0, 0);
+    return acc;
   };
 
   // the zero block that the kernels reading this launch's outputs take as
