@@ -116,6 +116,32 @@ struct Rows {
 
 constexpr int RB_LM = 20;         // row stride of the 16 x 16 matrices
 
+// acc + A r for a triangular 16 x 16 matrix in LDS (UPPER: zero left of the
+// diagonal, else right of it) and r in the result layout.  The matrix product
+// meets those zeros too, and a zero times a NaN or an infinity is a NaN: a
+// value column that holds one goes by the sum over its triangle alone, so
+// that no token reaches one on the other side of the diagonal.
+template <bool UPPER>
+__device__ inline f4 tri4(const float (*A)[RB_LM], f4 r, f4 acc, int lane) {
+  const int g = lane >> 4, m = lane & 15;
+  bool finite = true;
+#pragma unroll
+  for (int j = 0; j < 4; ++j) finite = finite && fabsf(r[j]) <= 3.402823466e+38f;
+  if (__all(finite)) return mf4(*(const f4*)&A[m][4 * g], r, acc);
+#pragma unroll 1
+  for (int i = 0; i < RB_TB; i += 4)
+#pragma unroll
+    for (int c = 0; c < 4; ++c) {
+      const float ri = lane_from(r[c], 4 * i + m);     // row i + c of this lane's column
+#pragma unroll
+      for (int j = 0; j < 4; ++j) {
+        const int t = 4 * g + j;
+        if (UPPER ? i + c >= t : i + c <= t) acc[j] += A[t][i + c] * ri;
+      }
+    }
+  return acc;
+}
+
 }  // namespace
 
 template <typename E, int DK, int DV>
@@ -302,8 +328,10 @@ __global__ __launch_bounds__(DV * 4) __attribute__((amdgpu_waves_per_eu(ONE ? 4 
         __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
         for (int c = (i + 2) / 4; c < 4; ++c) nxt[c] = *(const f4*)&sm.dGT[i + 1][4 * c];
+        if (m <= i) {                          // x[i] is zero above: no product with an A that may not be finite
 #pragma unroll
-        for (int r = i + 1; r < RB_TB; ++r) x[r] -= cur[r >> 2][r & 3] * x[i];
+          for (int r = i + 1; r < RB_TB; ++r) x[r] -= cur[r >> 2][r & 3] * x[i];
+        }
 #pragma unroll
         for (int c = (i + 2) / 4; c < 4; ++c) cur[c] = nxt[c];
       }
@@ -407,9 +435,9 @@ __global__ __launch_bounds__(DV * 4) __attribute__((amdgpu_waves_per_eu(ONE ? 4 
         dO[j] = tof(sm.dO[4 * g + j][v0 + m]);
         dd[j] = gb[j] * gk[j];
       }
-      const f4 e = mf4(*(const f4*)&sm.M[m][4 * g], r, zero4());
-      dd = mf4(*(const f4*)&sm.PT[m][4 * g], dO, dd);
-      wv = mf4(*(const f4*)&sm.MT[m][4 * g], dd, zero4());
+      const f4 e = tri4<false>(sm.M, r, zero4(), lane);
+      dd = tri4<true>(sm.PT, dO, dd, lane);
+      wv = tri4<true>(sm.MT, dd, zero4(), lane);
       f4 s1, s2, s3;
 #pragma unroll
       for (int j = 0; j < 4; ++j) {

@@ -121,3 +121,32 @@ def test_recurrent_bwd_without_state_gradients(T):
         assert torch.equal(full[key], part[key]), key
     errs = bwd_errors(d, part, skip=("d_initial_state",))
     assert all(v <= 1e-5 for v in errs.values()), errs
+
+
+@pytest.mark.parametrize("dt,T", [("f32", 12), ("bf16", 16), ("f32", 40)])
+@pytest.mark.parametrize("key,bad,later,same", [
+    ("v", float("inf"), False, ("dq", "dk", "dbeta", "dlam")), ("v", float("nan"), False, ("dq", "dk", "dbeta", "dlam")),
+    ("d_o", float("-inf"), True, ("dq", "dk", "dv", "dbeta", "dlam", "dlog_alpha")),
+    ("k", float("nan"), True, ("dv",)), ("q", float("nan"), True, ("dv",))])
+def test_recurrent_bwd_keeps_tokens_apart(dt, T, key, bad, later, same):
+    """A value that is not finite, in one token, leaves the gradients it does not enter as they were: those of the
+    earlier tokens where it is in v (dv does not depend on v at all), of the later ones where it is in d_o, and the
+    later dv where it is in k or q.  Up to the order of the sums in the block that holds it (fp32; bf16 gradients to
+    one rounding, 2^-8)."""
+    d = synth.make(2, T, 2, 64, 64, dt, "G3", seed=797, s0=True, with_do=True)
+    at = T // 2
+    ref = _rec_bwd(d, _dsf(d, 2))
+    d2 = dict(d, **{key: d[key].clone()})
+    d2[key][0, at, 1, 5] = bad
+    got = _rec_bwd(d2, _dsf(d, 2))
+    rows = slice(at + 1, None) if later else slice(None, at)
+    tol = 1e-5 if dt == "f32" else 2.0 ** -8
+    for name in same:
+        a, b = got[name][0, rows, 1], ref[name][0, rows, 1]
+        assert torch.isfinite(a).all(), name
+        assert float((a.float() - b.float()).abs().max()) <= tol * float(b.float().abs().max()), name
+    if key == "v":
+        assert torch.equal(got["dv"], ref["dv"])
+    assert not torch.isfinite(got["dk"][0, at, 1]).all()
+    for name in ("dq", "dk", "dv", "dbeta", "dlam"):        # the other heads and sequences
+        assert torch.equal(got[name][1], ref[name][1]) and torch.equal(got[name][0, :, 0], ref[name][0, :, 0]), name
