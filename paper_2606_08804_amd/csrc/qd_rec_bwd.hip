@@ -116,18 +116,22 @@ struct Rows {
 
 constexpr int RB_LM = 20;         // row stride of the 16 x 16 matrices
 
+// Whether all four are finite: 0 * x is 0 for those, NaN for the others.
+__device__ inline bool is_finite4(f4 x) {
+  const f4 z = 0.f * x;
+  return (z[0] + z[1]) + (z[2] + z[3]) == 0.f;
+}
+
 // acc + A r for a triangular 16 x 16 matrix in LDS (UPPER: zero left of the
 // diagonal, else right of it) and r in the result layout.  The matrix product
 // meets those zeros too, and a zero times a NaN or an infinity is a NaN: a
-// value column that holds one goes by the sum over its triangle alone, so
-// that no token reaches one on the other side of the diagonal.
+// wave whose r holds one goes by the sums over the triangle alone, so that no
+// token reaches one on the other side of the diagonal.  (The checks of r and
+// of A cost 1 to 3% of a call; checking the products instead cost 1 to 7%.)
 template <bool UPPER>
 __device__ inline f4 tri4(const float (*A)[RB_LM], f4 r, f4 acc, int lane) {
   const int g = lane >> 4, m = lane & 15;
-  bool finite = true;
-#pragma unroll
-  for (int j = 0; j < 4; ++j) finite = finite && fabsf(r[j]) <= 3.402823466e+38f;
-  if (__all(finite)) return mf4(*(const f4*)&A[m][4 * g], r, acc);
+  if (__all(is_finite4(r))) return mf4(*(const f4*)&A[m][4 * g], r, acc);
 #pragma unroll 1
   for (int i = 0; i < RB_TB; i += 4)
 #pragma unroll
@@ -303,6 +307,7 @@ __global__ __launch_bounds__(DV * 4) __attribute__((amdgpu_waves_per_eu(ONE ? 4 
       at[j] = t > m ? be[j] * gam[j] * xk[j] : 0.f;
       pt[j] = t >= m ? gam[j] * qk[j] : 0.f;
     }
+    const bool finite = __all(is_finite4(at));
     *(f4*)&sm.dGT[m][4 * g] = at;              // A^T
     *(f4*)&sm.PT[m][4 * g] = pt;
     f4* const keep = (f4*)(sm.x + SM::PB) + lane;
@@ -315,7 +320,7 @@ __global__ __launch_bounds__(DV * 4) __attribute__((amdgpu_waves_per_eu(ONE ? 4 
       if (g == 0) sm.gC = gC;
     }
     asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
-    if (lane < RB_TB) {
+    if (lane < RB_TB && finite) {
       // column m of M by substitution, column i of A read one step ahead
       float x[RB_TB];
 #pragma unroll
@@ -328,10 +333,8 @@ __global__ __launch_bounds__(DV * 4) __attribute__((amdgpu_waves_per_eu(ONE ? 4 
         __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
         for (int c = (i + 2) / 4; c < 4; ++c) nxt[c] = *(const f4*)&sm.dGT[i + 1][4 * c];
-        if (m <= i) {                          // x[i] is zero above: no product with an A that may not be finite
 #pragma unroll
-          for (int r = i + 1; r < RB_TB; ++r) x[r] -= cur[r >> 2][r & 3] * x[i];
-        }
+        for (int r = i + 1; r < RB_TB; ++r) x[r] -= cur[r >> 2][r & 3] * x[i];
 #pragma unroll
         for (int c = (i + 2) / 4; c < 4; ++c) cur[c] = nxt[c];
       }
@@ -339,6 +342,16 @@ __global__ __launch_bounds__(DV * 4) __attribute__((amdgpu_waves_per_eu(ONE ? 4 
       for (int r = 0; r < RB_TB; ++r) sm.M[r][m] = x[r];
 #pragma unroll
       for (int r = 0; r < RB_TB; r += 4) *(f4*)&sm.MT[m][r] = f4{x[r], x[r + 1], x[r + 2], x[r + 3]};
+    } else if (lane < RB_TB) {
+      // the same without the terms above the column's diagonal, whose zeros an A that is not finite must not meet
+#pragma unroll 1
+      for (int r = 0; r < RB_TB; ++r) {
+        float x = r == m ? 1.f : 0.f;
+#pragma unroll 1
+        for (int i = m; i < r; ++i) x -= sm.dGT[i][r] * sm.M[i][m];
+        sm.M[r][m] = x;
+        sm.MT[m][r] = x;
+      }
     }
   };
   // S k_t, S q_t (rows t, this wave's value columns)
