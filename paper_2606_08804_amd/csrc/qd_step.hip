@@ -8,6 +8,8 @@
 // fully coalesced 16-byte accesses, and the two row dot products are reduced
 // with DPP lane moves (one shuffle across rows of 16).  The kernel is bound by
 // HBM (or MALL) bandwidth.
+#include <type_traits>
+
 #include "qd_common.h"
 #include "qd_launch.h"
 
@@ -100,13 +102,11 @@ __global__ __launch_bounds__(NTHREADS) void k_step(int DV, int nrb, const E* __r
 // tokens [cu[n], cu[n+1]) when cu is given (clamped to [0, T_total]), else
 // [n T, (n + 1) T); token t of head h sits at row t H + h.
 template <typename E, int DK>
-__global__ __launch_bounds__(NTHREADS) void k_steps(int T, const int* __restrict__ cu, int T_total, int H,
-                                                  int DV, int nrb, const E* __restrict__ q,
-                                                  const E* __restrict__ k, const E* __restrict__ v,
-                                                  const float* __restrict__ beta,
-                                                  const float* __restrict__ lam, float lam_c,
-                                                  const float* __restrict__ la, const float* __restrict__ S0,
-                                                  float* __restrict__ S, E* __restrict__ o) {
+__global__ __launch_bounds__(NTHREADS) __attribute__((amdgpu_waves_per_eu(sizeof(E) == 4 ? 7 : 6))) void k_steps(
+    int T, const int* __restrict__ cu, int T_total, int H, int DV, int nrb, const E* __restrict__ q,
+    const E* __restrict__ k, const E* __restrict__ v, const float* __restrict__ beta, const float* __restrict__ lam,
+    float lam_c, const float* __restrict__ la, const float* __restrict__ S0, float* __restrict__ S,
+    E* __restrict__ o) {
   constexpr int LPR = DK / 4;            // lanes per state row
   constexpr int RPB = NTHREADS / LPR;    // rows per workgroup pass
   constexpr int RPT = STEP_RPT;          // passes (rows per lane group)
@@ -119,75 +119,82 @@ __global__ __launch_bounds__(NTHREADS) void k_steps(int T, const int* __restrict
   const int t0 = cu ? min(max(cu[n], 0), T_total) : n * T;
   const int t1 = cu ? min(max(cu[n + 1], t0), T_total) : t0 + T;
   size_t a = (size_t)t0 * H + u % H;     // row of the token
-  float qv[4], kv[4], bt, lm, la_, vr[RPT];
+  // Operands of a token: loaded as they lie in memory, with no branch on the
+  // row and no conversion among the loads (the compiler would wait for each by
+  // itself), and converted before the stores of the token in between (a wait
+  // after them would cover them too).  A long sequence among short ones walks
+  // alone here, at the latency of a token: 63 sequences of one token and one
+  // of 65, 16 heads, bf16, d 64: 73 us with a wait for each load, 43 so
+  // (d 128: 98, 68); 64 of two tokens, d 128: 28.6, 24.2.
+  typename Quad<E>::raw qr, kr;
+  E vr[RPT];
+  float qt[4], kt[4], vt[RPT], bt, lm, la_, bn, ln, an;
+  int vz = 0;                            // the gates by vector loads too: a wait for a scalar one is a wait for all
+  if constexpr (sizeof(E) == 2) asm volatile("" : "+v"(vz));
   auto load = [&]() {
+    qr = *(const typename Quad<E>::raw*)(q + a * DK + c0);
+    kr = *(const typename Quad<E>::raw*)(k + a * DK + c0);
+#pragma unroll
+    for (int i = 0; i < RPT; ++i) vr[i] = v[a * DV + min(row0 + i * RPB, DV - 1)];
+    ln = (lam ? lam : beta)[a + vz];
+    bn = beta[a + vz];
+    an = (la ? la : beta)[a + vz];
+  };
+  auto take = [&]() {
 #pragma unroll
     for (int j = 0; j < 4; ++j) {
-      qv[j] = tof(q[a * DK + c0 + j]);
-      kv[j] = tof(k[a * DK + c0 + j]);
+      qt[j] = Quad<E>::get(qr, j);
+      kt[j] = Quad<E>::get(kr, j);
+      asm volatile("" : "+v"(qt[j]), "+v"(kt[j])::"memory");
     }
-    lm = lam ? lam[a] : lam_c;
-    bt = beta[a];
-    la_ = la ? la[a] : 0.f;
-  };
-  auto load_v = [&]() {
 #pragma unroll
     for (int i = 0; i < RPT; ++i) {
-      const int row = row0 + i * RPB;
-      vr[i] = row < DV ? tof(v[a * DV + row]) : 0.f;
+      vt[i] = tof(vr[i]);
+      asm volatile("" : "+v"(vt[i])::"memory");
     }
+    bt = bn;
+    lm = lam ? ln : lam_c;
+    la_ = an;
+    asm volatile("" : "+v"(bt), "+v"(lm), "+v"(la_)::"memory");
   };
   f4 s[RPT];
+  if (S0) {                              // rows past DV repeat the last one, and are not stored
 #pragma unroll
-  for (int i = 0; i < RPT; ++i) {        // rows past DV: the whole lane group skips them
-    const int row = row0 + i * RPB;
-    s[i] = S0 && row < DV ? *(const f4*)(S0 + (u * DV + row) * DK + c0) : zero4();
+    for (int i = 0; i < RPT; ++i) s[i] = *(const f4*)(S0 + (u * DV + min(row0 + i * RPB, DV - 1)) * DK + c0);
+  } else {
+#pragma unroll
+    for (int i = 0; i < RPT; ++i) s[i] = zero4();
   }
-  if (t0 < t1) {
-    load();
-    load_v();
-  }
-  for (int t = t0; t < t1; ++t) {
+  auto token = [&](auto more) {
     const size_t at = a;
-    float qt[4], kt[4], xv[4], vt[RPT];
-    const float be = bt, lmt = lm, al = la ? __expf(la_) : 1.f;
-#pragma unroll
-    for (int j = 0; j < 4; ++j) {
-      qt[j] = qv[j];
-      kt[j] = kv[j];
-      xv[j] = kt[j] + lmt * qt[j];
-    }
-#pragma unroll
-    for (int i = 0; i < RPT; ++i) vt[i] = vr[i];
-    if (t + 1 < t1) {                    // the next token's operands, in flight during this one
+    if constexpr (decltype(more)::value) {   // the next token's operands, in flight during this one
       a += H;
       load();
-      load_v();
     }
+    const float al = la ? __expf(la_) : 1.f;
     float px[RPT];
 #pragma unroll
     for (int i = 0; i < RPT; ++i) {
       px[i] = 0.f;
 #pragma unroll
-      for (int j = 0; j < 4; ++j) px[i] += s[i][j] * xv[j];
+      for (int j = 0; j < 4; ++j) px[i] += s[i][j] * (kt[j] + lm * qt[j]);
     }
 #pragma unroll
     for (int i = 0; i < RPT; ++i) px[i] = row_sum<LPR>(px[i]);
     float oq[RPT];
 #pragma unroll
     for (int i = 0; i < RPT; ++i) {
-      const float e = be * (vt[i] - al * px[i]);
+      const float e = bt * (vt[i] - al * px[i]);
       oq[i] = 0.f;
 #pragma unroll
       for (int j = 0; j < 4; ++j) {
         s[i][j] = al * s[i][j] + e * kt[j];
         oq[i] += s[i][j] * qt[j];
       }
-      const int row = row0 + i * RPB;
-      if (row < DV && S && t + 1 == t1) *(f4*)(S + (u * DV + row) * DK + c0) = s[i];
     }
 #pragma unroll
     for (int i = 0; i < RPT; ++i) oq[i] = row_sum<LPR>(oq[i]);
+    if constexpr (decltype(more)::value) take();
     if ((tid % LPR) == 0) {
 #pragma unroll
       for (int i = 0; i < RPT; ++i) {
@@ -195,8 +202,14 @@ __global__ __launch_bounds__(NTHREADS) void k_steps(int T, const int* __restrict
         if (row < DV) o[at * DV + row] = fromf<E>(oq[i]);
       }
     }
+  };
+  if (t0 < t1) {
+    load();
+    take();
+    for (int t = t0; t + 1 < t1; ++t) token(std::true_type());
+    token(std::false_type());
   }
-  if (t0 == t1 && S) {                   // no token: the state passes through
+  if (S) {
 #pragma unroll
     for (int i = 0; i < RPT; ++i) {
       const int row = row0 + i * RPB;

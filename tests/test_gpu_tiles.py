@@ -61,6 +61,15 @@ def test_recurrent_fwd_packed_routes(lengths):
     assert all(v <= REC_TOL["f32"] for v in errs.values()), errs
 
 
+@pytest.mark.parametrize("dt,Dk,Dv", [("bf16", 64, 64), ("bf16", 128, 24), ("f32", 64, 72)])
+def test_recurrent_fwd_packed_skewed(dt, Dk, Dv):
+    """One long sequence among single tokens, still within the mean of the step route: every token's operands are
+    loaded while the one before is computed, the last one's with none after it."""
+    d = synth.make(1, 0, 3, Dk, Dv, dt, "G3", seed=757, lengths=[1] * 9 + [17, 0, 2] + [1] * 9, s0=True)
+    errs = fwd_errors(d, *_rec(d))
+    assert all(v <= REC_TOL[dt] for v in errs.values()), errs
+
+
 @pytest.mark.parametrize("T", [4, 12, 40])
 def test_recurrent_fwd_is_causal_and_takes_alpha_zero(T):
     """alpha = 0 (log alpha = -inf) forgets the state exactly; a NaN in one token leaves every earlier output as it was."""
