@@ -290,9 +290,9 @@ size_t qdelta_recurrent_workspace_bytes(int32_t B, int32_t T, int32_t H, int32_t
 /* Backward of the fully recurrent form (the paper ships kernels for both the
  * fully recurrent and the chunkwise form, Sec. 3.3): exact gradients (up to
  * rounding) of L = <d_o, o> + <d_final_state, final_state> through
- * Eq. (qdelta_decay), one launch, no saved context (the states are
- * recomputed).  Arguments and gradient conventions as
- * qdelta_chunk_bwd (dense layout; dlam per token for a lam tensor, one float
+ * Eq. (qdelta_decay), one launch (two for a packed batch of many short
+ * sequences), no saved context (the states are recomputed).  Arguments and
+ * gradient conventions as qdelta_chunk_bwd (dense layout; dlam per token for a lam tensor, one float
  * or NULL for a constant lambda), plus a workspace of
  * qdelta_recurrent_workspace_bytes.  Same results as qdelta_chunk_bwd up to
  * rounding; meant for short sequences, where the chunk form's per-chunk

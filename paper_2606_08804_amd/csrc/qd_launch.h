@@ -97,6 +97,7 @@ struct RecBwdArgs {
   void *dq, *dk, *dv;
   float *dbeta, *dlam, *dla, *dS0;
   float* wDL;               // per token-head gradient of a constant lambda (else nullptr)
+  int skip;                 // > 0: sequences of at most so many tokens are another launch's
   float* wS;                // workspace: stored entry states, [slot][H][DV][DK] fp32 (rec_ckpt)
 };
 
@@ -105,6 +106,9 @@ struct RecBwdArgs {
 // n_tok_heads entries) is written there.
 hipError_t launch_rec_bwd(const RecBwdArgs& a, int units, int dtype, int Dk, float* dlam_sum, long long n_tok_heads,
                           hipStream_t st);
+
+// The same for sequences of at most `tokens` tokens (1 or 2; up to 4 at Dk = 64); longer ones are left alone.
+hipError_t launch_rec_bwd_few(const RecBwdArgs& a, int units, int dtype, int Dk, int tokens, hipStream_t st);
 
 // Row L2 normalisation (bwd == 0: x -> out, rn_out) or its backward
 // (bwd == 1: y, rn_in, dy -> out).

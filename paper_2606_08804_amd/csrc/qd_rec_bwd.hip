@@ -203,6 +203,7 @@ __global__ __launch_bounds__(DV * 4) __attribute__((amdgpu_waves_per_eu(ONE ? 4 
     t0 = n * a.T;
     t1 = t0 + a.T;
   }
+  if (a.skip > 0 && t1 - t0 <= a.skip) return;
   const int nblk = (t1 - t0 + RB_TB - 1) / RB_TB;
   const E* const qp = (const E*)a.q + (size_t)h * DK;
   const E* const kp = (const E*)a.k + (size_t)h * DK;
@@ -672,21 +673,43 @@ __global__ __launch_bounds__(NTHREADS) void k_sum_floats(const float* x, long lo
 hipError_t launch_rec_bwd(const RecBwdArgs& a, int units, int dtype, int Dk, float* dlam_sum, long long n_tok_heads,
                           hipStream_t st) {
   if (units > 0) {
-    const bool one = !a.cu && a.T <= RB_TB;
+    // Sequences of a few tokens go to launch_rec_bwd_few: up to two, or four
+    // at d_k 64, d_v 256 (where a workgroup here takes a whole CU) while there
+    // are more of them than CUs.  The lengths of a packed batch are not known
+    // here: while their mean is within that and there are more units than CUs,
+    // both are launched, each for its sequences; below, where nothing but the
+    // launch and the longest sequence counts, these kernels take them all
+    // (packed, d 128, bf16: 64 x 16 units of one token 38 us in both launches,
+    // 77 in one; 63 of one and one of 65 tokens 171, 190; 16 x 16 units, 15 of
+    // one token and one of 17, 71, 47).
+    const bool full = units > device_cu_count();
+    const int limit = Dk == 64 && a.DV == 256 && full ? 4 : 2;
+    const bool few = a.cu ? full && a.T_total <= (long long)limit * (units / a.H) : a.T >= 1 && a.T <= limit;
+    if (few) {
+      prof_mark(ST_REC_BWD, 0, st);
+      const hipError_t e = launch_rec_bwd_few(a, units, dtype, Dk, a.cu ? limit : a.T, st);
+      prof_mark(ST_REC_BWD, 1, st);
+      if (e != hipSuccess) return e;
+    }
+    RecBwdArgs b = a;
+    b.skip = few ? limit : 0;
+    const bool one = !a.cu && a.T <= RB_TB, rest = !few || (a.cu && a.T_total > limit);
 #define QD_RB(ET, DKV, DVV)                                                                              \
   do {                                                                                                   \
-    if (one) hipLaunchKernelGGL((k_rec_bwd<ET, DKV, DVV, true>), dim3(units), dim3(DVV * 4), 0, st, a);  \
-    else hipLaunchKernelGGL((k_rec_bwd<ET, DKV, DVV, false>), dim3(units), dim3(DVV * 4), 0, st, a);     \
+    if (one) hipLaunchKernelGGL((k_rec_bwd<ET, DKV, DVV, true>), dim3(units), dim3(DVV * 4), 0, st, b);  \
+    else hipLaunchKernelGGL((k_rec_bwd<ET, DKV, DVV, false>), dim3(units), dim3(DVV * 4), 0, st, b);     \
   } while (0)
 #define QD_RB_V(ET, DKV)                                                                      \
   if (a.DV == 256) QD_RB(ET, DKV, 256); else if (a.DV == 128) QD_RB(ET, DKV, 128);            \
   else if (a.DV == 64) QD_RB(ET, DKV, 64); else QD_RB(ET, DKV, 32)
-    prof_mark(ST_REC_BWD, 0, st);
-    if (dtype == 1 && Dk == 128) { QD_RB_V(__bf16, 128); }
-    else if (dtype == 1 && Dk == 64) { QD_RB_V(__bf16, 64); }
-    else if (dtype == 0 && Dk == 128) { QD_RB_V(float, 128); }
-    else { QD_RB_V(float, 64); }
-    prof_mark(ST_REC_BWD, 1, st);
+    if (rest) {
+      prof_mark(ST_REC_BWD, 0, st);
+      if (dtype == 1 && Dk == 128) { QD_RB_V(__bf16, 128); }
+      else if (dtype == 1 && Dk == 64) { QD_RB_V(__bf16, 64); }
+      else if (dtype == 0 && Dk == 128) { QD_RB_V(float, 128); }
+      else { QD_RB_V(float, 64); }
+      prof_mark(ST_REC_BWD, 1, st);
+    }
 #undef QD_RB_V
 #undef QD_RB
   }

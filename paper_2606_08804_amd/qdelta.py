@@ -19,7 +19,7 @@ recurrent_step(q, k, v, beta, lam, log_alpha, state) -> o        (state updated 
 recurrent_fwd(q, k, v, beta, lam=None, log_alpha=None, initial_state=None, cu_seqlens=None)
           -> (o, final_state)                                  (token by token, one launch)
 recurrent_bwd(q, k, v, beta, lam, log_alpha, initial_state, d_o, d_final_state=None,
-          cu_seqlens=None) -> dict of gradients                (token by token, one launch)
+          cu_seqlens=None) -> dict of gradients                (of the recurrent form, no saved context)
 l2norm_fwd(x) -> (y, rnorm);  l2norm_bwd(y, rnorm, dy) -> dx   (row L2 norm for the layer's q, k)
 
 lam: a [.., H] fp32 tensor (per token and head), a number (one constant for every
@@ -451,7 +451,7 @@ def recurrent_workspace_bytes(B, T, H, Dk, Dv, n_seqs=0):
 
 def recurrent_bwd(q, k, v, beta, lam, log_alpha, initial_state, d_o, d_final_state=None, cu_seqlens=None,
                   need_d_initial_state=True, workspace=None):
-    """Backward of the fully recurrent form (token by token, one launch, no
+    """Backward of the fully recurrent form (one or two launches, no
     saved context).  Same layouts and returned gradients as chunk_bwd."""
     L = lib()
     dt = _dt(q)

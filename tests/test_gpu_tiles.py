@@ -98,7 +98,7 @@ def _dsf(d, N):
 
 
 @pytest.mark.parametrize("dt,Dk,Dv", [("bf16", 128, 128), ("f32", 128, 256), ("f32", 64, 32), ("bf16", 64, 64)])
-@pytest.mark.parametrize("T", [3, 15, 16, 17, 32, 33, 49, 97])
+@pytest.mark.parametrize("T", [1, 2, 3, 4, 5, 15, 16, 17, 32, 33, 49, 97])
 def test_recurrent_bwd_lengths(T, dt, Dk, Dv):
     """One block and several, on and beside the block edges and the spacing of the stored states (2 or 3 blocks),
     with a final-state gradient; alpha = 0 in one token.  fp32 sums: 1e-5 of the largest value."""
@@ -119,7 +119,39 @@ def test_recurrent_bwd_packed_stored_states(lengths):
     assert all(v <= 1e-5 for v in errs.values()), errs
 
 
-@pytest.mark.parametrize("T", [5, 40])
+@pytest.mark.parametrize("dt,Dk,Dv", [("bf16", 128, 128), ("f32", 64, 256), ("bf16", 64, 256), ("f32", 128, 32)])
+@pytest.mark.parametrize("lengths", [[1, 2, 0, 3] * 6, [1] * 23 + [17], [2, 0] * 12])
+def test_recurrent_bwd_packed_few(lengths, dt, Dk, Dv):
+    """Packed batches of more (sequence, head) pairs than CUs whose mean is within the few-token limit (2, 4 at d_k 64,
+    d_v 256): each sequence is one of two launches', by its length."""
+    H = 12
+    assert len(lengths) * H > 256 and sum(lengths) <= 2 * len(lengths)
+    d = synth.make(1, 0, H, Dk, Dv, dt, "G3", seed=787, lengths=lengths, s0=True, with_do=True)
+    d["log_alpha"][0, 1] = -np.inf
+    dsf = _dsf(d, len(lengths))
+    g = _rec_bwd(d, dsf)
+    heads = [0, H - 1]
+    g = {k: None if v is None else v[:, heads] if k == "d_initial_state" else v[:, :, heads] for k, v in g.items()}
+    errs = bwd_errors(select_heads(d, heads), g, dsf[:, heads])
+    tol = 1e-5 if dt == "f32" else REC_TOL[dt]
+    assert all(v <= tol for v in errs.values()), errs
+
+
+@pytest.mark.parametrize("dt", ["bf16", "f32"])
+@pytest.mark.parametrize("B,H,T", [(22, 12, 3), (22, 12, 4), (16, 16, 4)])
+def test_recurrent_bwd_few_tokens_wide_values(B, H, T, dt):
+    """Three and four tokens at d_k 64, d_v 256, with more units than CUs and with as many."""
+    d = synth.make(B, T, H, 64, 256, dt, "G3", seed=789, s0=True, with_do=True)
+    dsf = _dsf(d, B)
+    g = _rec_bwd(d, dsf)
+    heads = [0, H - 1]
+    g = {k: None if v is None else v[:, heads] if k == "d_initial_state" else v[:, :, heads] for k, v in g.items()}
+    errs = bwd_errors(select_heads(d, heads), g, dsf[:, heads])
+    tol = 1e-5 if dt == "f32" else REC_TOL[dt]
+    assert all(v <= tol for v in errs.values()), errs
+
+
+@pytest.mark.parametrize("T", [2, 5, 40])
 def test_recurrent_bwd_without_state_gradients(T):
     """No initial state, no final-state gradient, no initial-state gradient wanted: the same token gradients."""
     d = synth.make(2, T, 2, 128, 64, "f32", "G1", seed=791, with_do=True)
@@ -132,7 +164,7 @@ def test_recurrent_bwd_without_state_gradients(T):
     assert all(v <= 1e-5 for v in errs.values()), errs
 
 
-@pytest.mark.parametrize("dt,T", [("f32", 12), ("bf16", 16), ("f32", 40)])
+@pytest.mark.parametrize("dt,T", [("f32", 4), ("f32", 12), ("bf16", 16), ("f32", 40)])
 @pytest.mark.parametrize("key,bad,later,same", [
     ("v", float("inf"), False, ("dq", "dk", "dbeta", "dlam")), ("v", float("nan"), False, ("dq", "dk", "dbeta", "dlam")),
     ("d_o", float("-inf"), True, ("dq", "dk", "dv", "dbeta", "dlam", "dlog_alpha")),
