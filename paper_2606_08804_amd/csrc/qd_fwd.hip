@@ -1044,10 +1044,11 @@ static hipError_t launch_fwd_seg_t(const Params& p, hipStream_t st) {
                      dim3(seg_first_blocks(units, DV) + seg_map_blocks<DK, DV, BW>(units, p.n_seg)),
                      dim3(NCW * 64 + 256), 0, st, p);
   prof_mark(ST_SEG_MAPS, 1, st);
-  prof_mark(ST_SEG_COMPOSE, 0, st);
-  if (p.n_seg > 2)
+  if (p.n_seg > 2) {
+    prof_mark(ST_SEG_COMPOSE, 0, st);
     hipLaunchKernelGGL((k_seg_compose<DK, DV>), dim3(units * (DV / SEG_COMPOSE_RB)), dim3(NTHREADS), 0, st, p);
-  prof_mark(ST_SEG_COMPOSE, 1, st);
+    prof_mark(ST_SEG_COMPOSE, 1, st);
+  }
   prof_mark(ST_SEG_OUT, 0, st);
   if (out_wide)
     hipLaunchKernelGGL((k_scan_fwd<E, DK, DV, BW, NCW, SEG_OUT>), dim3(out8 * DV / BW), dim3(NCW * 64 + 256), 0,

@@ -95,6 +95,17 @@ def test_segmented_first_segment(B, T, H, Dk, Dv, dt, G):
         assert torch.equal(o[:, :n], o1[:, :n])
 
 
+@pytest.mark.parametrize("G,launches", [(2, 0), (3, 1)])
+def test_segmented_profile_counts_launches(G, launches):
+    """Two segments leave no map to compose: that stage reports no launch."""
+    d = synth.make(1, 385, 2, 64, 64, "bf16", "G2", seed=178)
+    qdelta.profile_begin()
+    seg_fwd(d, G)
+    prof = qdelta.profile_end()
+    assert prof["seg_compose"][1] == launches
+    assert prof["seg_maps"][1] == 1 and prof["seg_out"][1] == 1 and prof["prep_fwd"][1] == 1
+
+
 def test_segmented_empty_inputs():
     """T = 0 passes the initial state through; B = 0 launches nothing."""
     d = synth.make(2, 0, 2, 128, 128, "bf16", "G2", seed=175, s0=True)
