@@ -190,7 +190,8 @@ class QDeltaLayer(torch.nn.Module):
         bias = getattr(self, "lambda_bias", None)
         return (h.is_cuda and h.numel() > 0 and h.dtype in (torch.bfloat16, torch.float32)
                 and type(self).gates is QDeltaLayer.gates and "gates" not in self.__dict__
-                and (bias is None or bias.is_cuda and bias.dim() == 0 and bias.dtype in (torch.bfloat16, torch.float32)))
+                and (bias is None or bias.device == h.device and bias.dim() == 0
+                     and bias.dtype in (torch.bfloat16, torch.float32)))
 
     def _fused_gates(self, h):
         logits = self.w_gates(h)

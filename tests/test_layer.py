@@ -5,6 +5,7 @@ through projections, L2 norms and gate nonlinearities) with central
 differences of its forward.  The GPU layer itself is tested in
 tests/test_gpu_layer.py."""
 import math
+from types import SimpleNamespace
 
 import pytest
 import torch
@@ -137,3 +138,15 @@ def test_function_constant_lambda_gradcheck(oracle_core):
         return layer.qdelta_chunk(q, k, v, beta, lam_c, la, S0)
 
     assert torch.autograd.gradcheck(f, ts, eps=1e-6, atol=1e-7, rtol=1e-6)
+
+
+def test_gate_kernels_take_the_bias_on_the_inputs_device_only():
+    """A bias on another GPU than the input is left to the elementwise operations, which refuse it; the kernel would
+    read it there."""
+    m = layer.QDeltaLayer(d_model=8, n_heads=2, head_dk=64, head_dv=64)
+    h = SimpleNamespace(is_cuda=True, device=torch.device("cuda", 0), dtype=torch.float32, numel=lambda: 8)
+    del m.lambda_bias
+    for index, ok in ((0, True), (1, False)):
+        m.__dict__["lambda_bias"] = SimpleNamespace(is_cuda=True, device=torch.device("cuda", index),
+                                                    dtype=torch.float32, dim=lambda: 0)
+        assert m._can_fuse_gates(h) == ok
