@@ -275,6 +275,61 @@ def test_recurrent_fwd_rejects_bad_arguments():
     assert L.qdelta_recurrent_fwd_varlen(8, 1, None, 1, 64, 64, 1, *args) == E.QDELTA_EINVAL
 
 
+def test_layer_entries_reject_bad_arguments():
+    """The entry points of the layer's own path validate before any launch; everything valid shows as
+    QDELTA_ENOWORKSPACE with one byte of workspace."""
+    L = qdelta.lib()
+    E = qdelta
+    f = FAKE
+
+    def fwd(B=2, T=8, N=2, cu=None, H=1, Dk=64, Dv=64, dtype=1, qkv=f, beta=f, lam=f, la=None, S0=None, q=f, k=f, rq=f,
+            rk=f, o=f, Sf=None, saved=None, ws=f, ws_bytes=1):
+        return L.qdelta_layer_fwd(B, T, N, cu, H, Dk, Dv, dtype, qkv, beta, lam, 0.5, la, S0, q, k, rq, rk, o, Sf,
+                                  saved, ws, ws_bytes, None)
+
+    def bwd(B=2, T=8, N=2, cu=None, H=1, Dk=64, Dv=64, dtype=1, qkv=f, q=f, k=f, rq=f, rk=f, beta=f, lam=f, la=None,
+            S0=None, saved=f, dO=f, dSf=None, dqkv=f, dbeta=f, dlam=f, dla=None, dS0=None, ws=f, ws_bytes=1):
+        return L.qdelta_layer_bwd(B, T, N, cu, H, Dk, Dv, dtype, qkv, q, k, rq, rk, beta, lam, 0.5, la, S0, saved, dO,
+                                  dSf, dqkv, dbeta, dlam, dla, dS0, ws, ws_bytes, None)
+
+    for call in (fwd, bwd):
+        assert call() == call(B=0, T=8, N=1, cu=f) == call(lam=None, **({"dlam": None} if call is bwd else {})) \
+            == E.QDELTA_ENOWORKSPACE
+        for name in ("qkv", "q", "k", "rq", "rk", "beta"):
+            assert call(**{name: None}) == E.QDELTA_EINVAL, (call.__name__, name)
+            assert call(**{name: f + 4}) == E.QDELTA_EINVAL, (call.__name__, name)
+        for name in ("lam", "la", "S0"):
+            assert call(**{name: f + 8}) == E.QDELTA_EINVAL, (call.__name__, name)
+        assert call(H=0) == call(T=-1) == call(B=-1) == call(dtype=3) == call(ws=None) == E.QDELTA_EINVAL
+        assert call(N=-1, cu=f) == E.QDELTA_EINVAL
+        assert call(Dk=96) == call(Dv=32) == call(Dk=128, dtype=0) == E.QDELTA_EUNSUPPORTED
+    assert fwd(o=None) == fwd(Sf=f + 4) == fwd(saved=f + 4) == E.QDELTA_EINVAL
+    for name in ("saved", "dO", "dqkv", "dbeta", "dlam"):
+        assert bwd(**{name: None}) == bwd(**{name: f + 4}) == E.QDELTA_EINVAL, name
+    assert bwd(la=f) == bwd(dla=f) == E.QDELTA_EINVAL        # log alpha without its gradient, and the other way round
+    assert bwd(dSf=f + 4) == bwd(dS0=f + 4) == E.QDELTA_EINVAL
+
+
+def test_layer_gate_entries_reject_bad_arguments():
+    L = qdelta.lib()
+    E = qdelta
+    f = FAKE
+
+    def fwd(tokens=8, H=2, dtype=1, bias_dtype=1, x=f, bias=f, beta=f, lam=f, la=f):
+        return L.qdelta_layer_gates_fwd(tokens, H, dtype, bias_dtype, x, bias, beta, lam, la, None)
+
+    def bwd(tokens=8, H=2, dtype=1, bias_dtype=1, beta=f, lam=f, la=f, dx=f, parts=f, dbias=f):
+        return L.qdelta_layer_gates_bwd(tokens, H, dtype, bias_dtype, beta, lam, la, f, f, f, dx, parts, dbias, None)
+
+    for call in (fwd, bwd):
+        assert call(tokens=0) == call(tokens=-1) == call(H=0) == call(tokens=1 << 30, H=2) == E.QDELTA_EINVAL
+        assert call(dtype=2) == call(bias_dtype=-1) == call(beta=None) == E.QDELTA_EINVAL
+    assert fwd(x=None) == fwd(bias=None) == E.QDELTA_EINVAL
+    assert bwd(dx=None) == bwd(parts=None) == bwd(dbias=None) == E.QDELTA_EINVAL
+    assert L.qdelta_layer_gate_parts(0, 2) == L.qdelta_layer_gate_parts(8, 0) == 0
+    assert L.qdelta_layer_gate_parts(300, 2) == 3             # one float per 256 (token, head) pairs, at most 1024
+
+
 def test_l2norm_rejects_bad_arguments():
     L = qdelta.lib()
     E = qdelta
