@@ -446,7 +446,11 @@ constexpr int intra_per_cu() { return sizeof(E) == 2 ? 2 : 1; }
 
 // NORM: q and k are L2-normalised rows; the kernel applies the backward of the
 // normalisation to its dq and dk while it holds them (a pass of its own over
-// them reads and writes 4 x 67 MB at B4 T4096 H16 d128, and took 71 us).
+// them reads and writes 4 x 67 MB at B4 T4096 H16 d128, and took 71 us).  dq
+// and dk are rounded to their type first, as that pass would read them, so
+// that a layer's gradients do not depend on which of the two routes a call
+// takes (unrounded they differed by 3.2e-3, at 5.3e-3 instead of 5.5e-3 from
+// the exact ones; now by 2.7e-5, the order of the sum y . dy).
 template <typename E, int DK, int DV, bool NORM>
 __global__ __launch_bounds__(INTRA_THREADS) __attribute__((amdgpu_waves_per_eu(intra_per_cu<E>(), intra_per_cu<E>()))) void k_bwd_intra(Params p) {
   constexpr int KS = Mma<E>::KS;
@@ -913,6 +917,8 @@ __global__ __launch_bounds__(INTRA_THREADS) __attribute__((amdgpu_waves_per_eu(i
       if constexpr (NORM) {
 #pragma unroll
         for (int j = 0; j < 4; ++j) {
+          oq[j] = tof(fromf<E>(oq[j]));    // as dq and dk themselves would be stored
+          ok[j] = tof(fromf<E>(ok[j]));
           yq += Quad<E>::get(qq, j) * oq[j];
           yk += Quad<E>::get(kq, j) * ok[j];
         }
