@@ -77,7 +77,7 @@ hipError_t launch_rec_fwd(int N, int T, const int* cu, int T_total, int H, int D
 // The recurrent backward stores the entry state of every rec_ckpt-th block of
 // 16 tokens.  The workspace holds 3 Dv + Dk floats per token and head
 // (qdelta_recurrent_workspace_bytes), so the spacing is the smallest whose
-// states fit: 2, or 3 at Dk = 128 with Dv = 256.
+// states fit: 1 at Dk = 64 with Dv = 32 or 64, 3 at Dk = 128 with Dv = 256, else 2.
 __host__ __device__ constexpr int rec_ckpt(int Dk, int Dv) {
   int c = 1;
   while (16 * c * (3 * Dv + Dk) < Dv * Dk) ++c;

@@ -100,8 +100,8 @@ def _dsf(d, N):
 @pytest.mark.parametrize("dt,Dk,Dv", [("bf16", 128, 128), ("f32", 128, 256), ("f32", 64, 32), ("bf16", 64, 64)])
 @pytest.mark.parametrize("T", [1, 2, 3, 4, 5, 15, 16, 17, 32, 33, 49, 97])
 def test_recurrent_bwd_lengths(T, dt, Dk, Dv):
-    """One block and several, on and beside the block edges and the spacing of the stored states (2 or 3 blocks),
-    with a final-state gradient; alpha = 0 in one token.  fp32 sums: 1e-5 of the largest value."""
+    """One block and several, on and beside the block edges and the spacing of the stored states (2, 3, 1 and 1 blocks
+    at these sizes), with a final-state gradient; alpha = 0 in one token.  fp32 sums: 1e-5 of the largest value."""
     d = synth.make(2, T, 3, Dk, Dv, dt, "G3", seed=770 + T, s0=True, with_do=True)
     d["log_alpha"][1, T // 2] = -np.inf
     dsf = _dsf(d, 2)
@@ -110,10 +110,13 @@ def test_recurrent_bwd_lengths(T, dt, Dk, Dv):
     assert all(v <= tol for v in errs.values()), errs
 
 
-@pytest.mark.parametrize("lengths", [[16, 0, 17, 1, 33, 50, 15], [40, 31, 32, 33, 1, 64]])
-def test_recurrent_bwd_packed_stored_states(lengths):
-    """The stored states of packed sequences that start anywhere within a block do not overlap."""
-    d = synth.make(1, 0, 2, 64, 64, "f32", "G2", seed=781, lengths=lengths, s0=True, with_do=True)
+@pytest.mark.parametrize("Dk,Dv", [(64, 64), (128, 128), (128, 256)])
+@pytest.mark.parametrize("lengths", [[16, 0, 17, 1, 33, 50, 15], [40, 31, 32, 33, 1, 64],
+                                     [5, 81, 97, 50, 0, 113, 65, 49], [47, 49, 98, 33, 96, 1, 130]])
+def test_recurrent_bwd_packed_stored_states(lengths, Dk, Dv):
+    """The stored states of packed sequences that start anywhere within a block, or within a group of the 1, 2 or 3
+    blocks between stored states, do not overlap, and the blocks between are walked again from the right one."""
+    d = synth.make(1, 0, 2, Dk, Dv, "f32", "G2", seed=781, lengths=lengths, s0=True, with_do=True)
     dsf = _dsf(d, len(lengths))
     errs = bwd_errors(d, _rec_bwd(d, dsf), dsf)
     assert all(v <= 1e-5 for v in errs.values()), errs
