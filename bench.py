@@ -159,7 +159,8 @@ def handoff_bytes_per_unit(stage, Dk, Dv, e, saved=True):
 # Sources of the kernels whose counters are stored: the kernel files and the
 # workspace layout.  A stored summary applies only while they hash to the
 # digest stored with it.
-KERNEL_SOURCES = ("qd_api.hip", "qd_bwd.hip", "qd_common.h", "qd_fwd.hip", "qd_rec_bwd.hip", "qd_step.hip")
+KERNEL_SOURCES = ("qd_api.hip", "qd_bwd.hip", "qd_common.h", "qd_fwd.hip", "qd_launch.h", "qd_rec_bwd.hip",
+                  "qd_rec_bwd_few.hip", "qd_step.hip")
 
 
 def strip_comments(src):
