@@ -282,8 +282,10 @@ int qdelta_recurrent_fwd_varlen(int32_t T, int32_t N, const int32_t* cu_seqlens,
 
 /* Workspace bytes of qdelta_recurrent_bwd[_varlen] for these sizes
  * (n_seqs == 0: dense B x T; n_seqs > 0: varlen, T total tokens): per
- * token-head 3 Dv + Dk + 1 fp32, per (sequence, head) Dv fp32.  0 for
- * unsupported sizes. */
+ * token-head 3 Dv + Dk + 1 fp32, per (sequence, head) Dv fp32 (kept for callers
+ * that size it so; the kernels fill less: the states at every first, second or
+ * third block of 16 tokens, and a float per token-head for a constant lambda's
+ * gradient).  0 for unsupported sizes. */
 size_t qdelta_recurrent_workspace_bytes(int32_t B, int32_t T, int32_t H, int32_t Dk, int32_t Dv,
                                         int32_t n_seqs);
 

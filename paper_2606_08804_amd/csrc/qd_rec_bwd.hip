@@ -38,11 +38,16 @@
 // rec_ckpt-th entry state; the reverse walk starts each block from the last
 // stored state before it.
 //
-// Bound by the fp32 matrix instructions (9 products of 16 Dk Dv per block, 29 us
-// for 1024 units at d 128) beside two or three passes over the states.
-// 64 sequences x 16 heads x 16 tokens, d 128, bf16: row sums on the vector ALU
-// over three token sweeps took 196 us (64 tokens
-// 680 us), this form 56 us (425 us).
+// A block is four products of 16 Dk Dv with S, two more for the gradient of the
+// state before it and two with a gradient of the state after it (3.4 us each
+// for 1024 units at d 128).  Bound by none of its resources alone but by the
+// chain of its phases: 64 sequences x 16 heads x 16 tokens, d 128, bf16 (six
+// products) keep the matrix cores 39% busy and move 169 MB at 3.0 TB/s, two
+// workgroups to a CU; past one block there is one to a CU (64 tokens: 37% busy,
+// 560 MB at 1.3 TB/s).  At d_v 256 sixteen waves leave 128 registers each, and
+// the form of several blocks spills (63 bf16 and 51 fp32 at d_k 128, 4 at 64).
+// Row sums on the vector ALU over three token sweeps took 196 us for 16 tokens
+// and 680 for 64, this form takes 56 and 425.
 #include "qd_common.h"
 #include "qd_launch.h"
 
@@ -681,7 +686,11 @@ hipError_t launch_rec_bwd(const RecBwdArgs& a, int units, int dtype, int Dk, flo
     // launch and the longest sequence counts, these kernels take them all
     // (packed, d 128, bf16: 64 x 16 units of one token 38 us in both launches,
     // 77 in one; 63 of one and one of 65 tokens 171, 190; 16 x 16 units, 15 of
-    // one token and one of 17, 71, 47).
+    // one token and one of 17, 71, 47).  Past that they take a packed batch in
+    // one launch also where its mean is within a block: the one-block form and
+    // the other one after each other take 61 us instead of 79 where all 64
+    // sequences have 3 to 16 tokens, but 327 instead of 270 where a quarter have
+    // 40 and a quarter 17 (and 29 instead of 27, 104 instead of 79 at d 64).
     const bool full = units > device_cu_count();
     const int limit = Dk == 64 && a.DV == 256 && full ? 4 : 2;
     const bool few = a.cu ? full && a.T_total <= (long long)limit * (units / a.H) : a.T >= 1 && a.T <= limit;

@@ -338,13 +338,15 @@ __device__ inline f4 rec_tok4(const E* k, int ld, int kt, int lane) {
 
 // Value blocks per wave where the launch fills the chip: wide tiles share the
 // K, Q reads and the Gram products over more rows, as many as the register
-// file takes at two waves per SIMD or more.
+// file takes at two waves per SIMD or more (bf16, d_k 128: four take 256 and
+// spill 19, 48 bytes a lane, and are still the faster: 88 us against 121 in
+// 16-row tiles for 64 sequences of 64 tokens, 16 heads, d 128).
 template <typename E, int DK>
 constexpr int rec_wide() { return sizeof(E) == 2 && DK == 128 ? 4 : 2; }
 // Waves per SIMD that the register need allows (the state takes 4 VB DK / 16
 // registers of a lane, the next block's pieces and the products the rest).
 template <typename E, int DK, int VB>
-constexpr int rec_waves() { return sizeof(E) == 4 ? (DK == 64 ? 2 : VB == 1 ? 2 : 2) : VB == 4 ? 2 : VB == 2 ? 3 : DK == 128 ? 2 : 4; }
+constexpr int rec_waves() { return sizeof(E) == 4 ? 2 : VB == 4 ? 2 : VB == 2 ? 3 : DK == 128 ? 2 : 4; }
 
 template <typename E, int DK, int VB>
 __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(rec_waves<E, DK, VB>(), rec_waves<E, DK, VB>()))) void k_rec_fwd(
@@ -588,11 +590,15 @@ hipError_t launch_rec_fwd(int N, int T, const int* cu, int T_total, int H, int D
   // A few tokens per sequence go through the step kernel: many short waves
   // with one read and one write of the state overlap better than one round of
   // long ones, until its row sums cost more.  16 heads, d 128, 64 sequences:
-  // bf16 T = 1 / 2 / 4 / 6: 24 / 28 / 37 / 47 us against 39 in blocks; fp32
-  // T = 4 / 6 / 8: 32 / 40 / 47 against 45; one sequence, T = 4 / 6 / 8: bf16
-  // 6.1 / 8.1 / 10.2 against 7.1, fp32 5.4 / 7.0 / 8.7 against 7.5.  Packed
-  // lengths are not known here: their mean decides, and lower, since one long
-  // sequence would walk alone.
+  // bf16 T = 1 / 2 / 4 / 6 / 8: 22 / 24 / 28 / 34 / 41 us against 36 in blocks;
+  // fp32 T = 4 / 6 / 8 / 10: 28 / 34 / 40 / 45 against 44; d_k 128, d_v 256, bf16
+  // T = 4 / 6 / 8: 54 / 69 / 86 against 70; d 64 13 against 14 up to T = 6.  (The
+  // lines stand at 4 and 6 from before the operands were loaded ahead; by these
+  // times they could be at 6 and 8.)  Packed lengths are not known here: their
+  // mean decides, and lower, since one long sequence walks alone: 63 of one
+  // token and one of 65: d 128 bf16 67 us against 74 in blocks, fp32 68 against
+  // 70, d 64 bf16 43 against 29 (one of 300: 233 against 212, fp32 245 against
+  // 165, d 64 182 against 80).
   if (cu ? T_total <= 2LL * N : T >= 1 && T <= (dtype == 1 ? 4 : 6))
     return step_at(N, T, cu, T_total, H, Dk, Dv, dtype, q, k, v, beta, lam, lam_c, la, S0, Sfin, o, st);
   const int units = N * H;
